@@ -268,11 +268,12 @@ int ec_tc_forward(const ec_problem *p, int32_t top_k, const void *X, const void 
  * events[s+1] after stage s, for s < n_events - 1, so that
  * hipEventElapsedTime(events[s], events[s+1]) is the duration of stage s.
  * The caller creates and owns the events; pass NULL / 0 to stop recording.
- * Stages of ec_moe_forward: 0 router+softmax, 1 top-k, 2 gather,
+ * Stages of ec_moe_forward: 0 router+softmax, 1 top-k, 2 gather
+ *   (only the fp32 saved buffer's Xe),
  *   3 W1/W3 grouped GEMM + SwiGLU, 4 W2 grouped GEMM, 5 shared W1/W3 + SwiGLU,
  *   6 shared W2, 7 combine (5 and 6 are empty without shared experts).
- * Stages of ec_moe_backward: 0 dY gather (empty for bf16: the dA product
- *   reads the selected rows itself), 1 dA grouped GEMM + SwiGLU backward + gate
+ * Stages of ec_moe_backward: 0 dY gather (empty: the dA and dW2 products
+ *   read the selected rows themselves), 1 dA grouped GEMM + SwiGLU backward + gate
  *   gradient partials, 2 dW2, 3 dXe, 4 dW1/dW3, 5 router dZ, 6 router dX,
  *   7 shared dA + SwiGLU backward, 8 shared dW2, 9 shared dX, 10 shared
  *   dW1/dW3 (7-10 empty without shared experts), 11 combine of dXe, 12 dWg.

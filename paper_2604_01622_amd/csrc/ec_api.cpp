@@ -132,9 +132,10 @@ Saved carve_saved(Carve& c, const Plan& P, bool with_h) {
   s.sel = (int32_t*)c.take((size_t)P.E * P.K * 4);
   s.gate = (float*)c.take((size_t)P.E * P.K * 4);
   s.slot = (int32_t*)c.take((size_t)P.E * P.N * 4);
-  // bf16 reads the selected rows of X inside the products that use them (the
-  // forward's W1/W3, the backward's dW1/dW3) and needs no gathered copy
-  s.Xe = (P.dtype != EC_BF16) ? c.take((size_t)P.E * P.K * P.d * P.esz) : nullptr;
+  // the products that use the selected rows of X (the forward's W1/W3, the
+  // backward's dW1/dW3) read them from X; only the fp32 saved buffer holds a
+  // gathered copy, which the fp32 dW1/dW3 product reads
+  s.Xe = (with_h && P.dtype != EC_BF16) ? c.take((size_t)P.E * P.K * P.d * P.esz) : nullptr;
   s.H1 = with_h ? c.take((size_t)P.E * P.K * P.h * P.esz) : nullptr;
   s.H3 = with_h ? c.take((size_t)P.E * P.K * P.h * P.esz) : nullptr;
   s.A = c.take((size_t)P.E * P.K * P.h * P.esz);
@@ -147,11 +148,10 @@ Saved carve_saved(Carve& c, const Plan& P, bool with_h) {
 }
 
 struct BwdWs {
-  void* dYe;      // [E, K, d] fp32: selected rows of dY; then dXe (both dtypes)
+  void* dXe;      // [E, K, d]
   float* dsp;     // [E, K, dsp_parts(h)] gate-gradient partials of the dA product
   void* dH;       // [E, K, 2h]
-  float* dZ;      // [N, E]
-  uint16_t* dZb;  // [N, EP] (bf16 only)
+  void* dZ;       // [N, EP]
   float* part;    // [splits, E, d]
   int splits;
   void* dHs;      // [N, 2 hs] shared experts' dH1 | dH3
@@ -161,11 +161,10 @@ struct BwdWs {
 
 BwdWs carve_bwd(Carve& c, const Plan& P) {
   BwdWs w;
-  w.dYe = c.take((size_t)P.E * P.K * P.d * P.esz);
+  w.dXe = c.take((size_t)P.E * P.K * P.d * P.esz);
   w.dsp = (float*)c.take((size_t)P.E * P.K * ec::dsp_parts(P.dtype, P.h) * 4);
   w.dH = c.take((size_t)P.E * P.K * 2 * P.h * P.esz);
-  w.dZ = (float*)c.take((size_t)P.N * P.E * 4);
-  w.dZb = P.dtype == EC_BF16 ? (uint16_t*)c.take((size_t)P.N * P.EP * 2) : nullptr;
+  w.dZ = c.take((size_t)P.N * P.EP * P.esz);
   w.splits = ec::router_dwg_splits(P.N, P.E, P.d);
   w.part = (float*)c.take((size_t)w.splits * P.E * P.d * 4);
   w.dHs = nullptr;
@@ -302,7 +301,6 @@ struct TcFwdWs {
   int32_t* slot;
   int32_t* rows;
   int32_t* sel;
-  void* Xe;
   void* A;
   void* O;
   void* As;
@@ -315,7 +313,6 @@ TcFwdWs carve_tc_fwd(Carve& c, const Plan& P, long rmax) {
   w.slot = (int32_t*)c.take((size_t)P.E * P.N * 4);
   w.rows = (int32_t*)c.take((size_t)(P.E + 1) * 4);
   w.sel = (int32_t*)c.take((size_t)rmax * 4);
-  w.Xe = P.dtype == EC_BF16 ? nullptr : c.take((size_t)rmax * P.d * P.esz);   // fp32 only
   w.A = c.take((size_t)rmax * P.h * P.esz);
   w.O = c.take((size_t)rmax * P.d * P.esz);
   w.As = P.hs ? c.take((size_t)P.N * P.hs * P.esz) : nullptr;
@@ -612,18 +609,12 @@ int ec_moe_forward(const ec_problem* p, const void* X, const void* Wg, const voi
   // The gate multiplies each expert row inside the W1/W3 product's epilogue
   // (A = g SiLU(H1) H3, so O = A W2^T is already gate-weighted and the combine
   // adds rows with weight 1).
-  if (P.dtype == EC_BF16) {
-    // the W1/W3 product reads the selected rows of X itself (the gather stage is
-    // empty)
-    EC_HIP(mark(3, stream));
-    EC_HIP(ec::launch_gemm_w13(P.dtype, X, W1, W3, s.A, s.H1, s.H3, P.E, M, P.d, P.h, stream,
-                               false, s.sel, s.gate));
-  } else {
-    EC_HIP(ec::launch_gather(P.dtype, X, s.sel, s.Xe, (long)P.E * M, P.d, P.N, stream));
-    EC_HIP(mark(3, stream));
-    EC_HIP(ec::launch_gemm_w13(P.dtype, s.Xe, W1, W3, s.A, s.H1, s.H3, P.E, M, P.d, P.h, stream,
-                               false, nullptr, s.gate));
-  }
+  // The W1/W3 product reads the selected rows of X itself; the gather stage is empty
+  // but for the copy that the fp32 saved buffer holds.
+  if (s.Xe) EC_HIP(ec::launch_gather(P.dtype, X, s.sel, s.Xe, (long)P.E * M, P.d, P.N, stream));
+  EC_HIP(mark(3, stream));
+  EC_HIP(ec::launch_gemm_w13(P.dtype, X, W1, W3, s.A, s.H1, s.H3, P.E, M, P.d, P.h, stream, false,
+                             s.sel, s.gate));
   EC_HIP(mark(4, stream));
   EC_HIP(ec::launch_gemm_w2(P.dtype, s.A, W2, s.O, P.E, M, P.d, P.h, stream, false));
   EC_HIP(mark(5, stream));
@@ -683,34 +674,27 @@ int ec_moe_backward(const ec_problem* p, const void* X, const void* Wg, const vo
   const BwdWs w = carve_bwd(c, P);
   const int M = (int)P.K;
   const int E = P.E, d = P.d, h = P.h, N = P.N, hs = P.hs;
-  void* dYe = w.dYe;  // [E, K, d] the selected rows of dY (not gate-scaled), fp32 only
-  void* dXe = w.dYe;  // dYe is dead once dW2 is formed
   // The saved A carries the gate (A = g SiLU(H1) H3), so dW2 = dYe^T A; the
   // dA product scales its rows by g (dA = g dYe W2) and its epilogue also sums
   // dA * SiLU(H1) H3 per row: the gate's gradient times the gate.
-  // bf16: dA and dXe = dH1 W1 + dH3 W3 read the weights K-major; dA and dW2
-  // read the selected rows of dY, dW1/dW3 those of X, inside their operand
-  // loads (the gather stage is empty and no gathered copy exists).
+  // dA and dW2 read the selected rows of dY, dW1/dW3 those of X (fp32: the saved
+  // copy), inside their operand loads; the gather stage is empty.
   EC_HIP(mark(0, stream));
-  const bool bf = P.dtype == EC_BF16;
-  if (!bf) EC_HIP(ec::launch_gather(P.dtype, dY, s.sel, dYe, (long)E * M, d, N, stream));
   EC_HIP(mark(1, stream));
-  EC_HIP(ec::launch_gemm_dA(P.dtype, bf ? dY : dYe, W2, s.H1, s.H3, w.dH, E, M, d, h, stream,
-                            false, w.dsp, bf ? s.sel : nullptr, s.gate));
+  EC_HIP(ec::launch_gemm_dA(P.dtype, dY, W2, s.H1, s.H3, w.dH, E, M, d, h, stream, false, w.dsp,
+                            s.sel, s.gate));
   EC_HIP(mark(2, stream));
-  EC_HIP(ec::launch_gemm_dW2(P.dtype, bf ? dY : dYe, s.A, dW2, E, M, d, h, stream,
-                             bf ? s.sel : nullptr));
+  EC_HIP(ec::launch_gemm_dW2(P.dtype, dY, s.A, dW2, E, M, d, h, stream, s.sel));
   EC_HIP(mark(3, stream));
-  EC_HIP(ec::launch_gemm_dXe(P.dtype, w.dH, W1, W3, dXe, E, M, d, h, stream, false));
+  EC_HIP(ec::launch_gemm_dXe(P.dtype, w.dH, W1, W3, w.dXe, E, M, d, h, stream, false));
   EC_HIP(mark(4, stream));
-  EC_HIP(ec::launch_gemm_dW13(P.dtype, w.dH, bf ? X : s.Xe, dW1, dW3, E, M, d, h, stream,
-                              bf ? s.sel : nullptr));
+  EC_HIP(ec::launch_gemm_dW13(P.dtype, w.dH, s.Xe ? s.Xe : X, dW1, dW3, E, M, d, h, stream,
+                              s.Xe ? nullptr : s.sel));
   EC_HIP(mark(5, stream));
-  EC_HIP(ec::launch_router_dz(s.S, w.dsp, ec::dsp_parts(P.dtype, h), s.slot, w.dZ, w.dZb, N, E, P.EP, M,
-                              p->inv_temperature, stream));
+  EC_HIP(ec::launch_router_dz(P.dtype, s.S, w.dsp, ec::dsp_parts(P.dtype, h), s.slot, w.dZ, N, E,
+                              P.EP, M, p->inv_temperature, stream));
   EC_HIP(mark(6, stream));
-  const void* dZop = P.dtype == EC_BF16 ? (const void*)w.dZb : (const void*)w.dZ;
-  EC_HIP(ec::launch_router_dx(P.dtype, dZop, Wg, dX, N, E, P.EP, d, stream));
+  EC_HIP(ec::launch_router_dx(P.dtype, w.dZ, Wg, dX, N, E, P.EP, d, stream));
   EC_HIP(mark(7, stream));
   if (hs && N > 0) {
     // shared experts: their output gradient is dY itself (no gate)
@@ -733,9 +717,9 @@ int ec_moe_backward(const ec_problem* p, const void* X, const void* Wg, const vo
     EC_HIP(mark(10, stream));
   }
   EC_HIP(mark(11, stream));
-  EC_HIP(ec::launch_bwd_combine(P.dtype, dXe, s.slot, dX, dX, N, E, M, d, stream));
+  EC_HIP(ec::launch_bwd_combine(P.dtype, w.dXe, s.slot, dX, dX, N, E, M, d, stream));
   EC_HIP(mark(12, stream));
-  EC_HIP(ec::launch_router_dwg(P.dtype, dZop, X, dWg, w.part, w.splits, N, E, P.EP, d, stream));
+  EC_HIP(ec::launch_router_dwg(P.dtype, w.dZ, X, dWg, w.part, w.splits, N, E, P.EP, d, stream));
   EC_HIP(mark(13, stream));
   return EC_OK;
 }
@@ -824,17 +808,10 @@ int ec_tc_forward(const ec_problem* p, int32_t top_k, const void* X, const void*
   const TcFwdWs w = carve_tc_fwd(c, P, rmax);
   int32_t* rows = expert_rows ? expert_rows : w.rows;
   EC_TRY(enqueue_tc_route(p, P, top_k, X, Wg, w.S, w.G, w.slot, rows, w.sel, rw, stream));
-  if (P.dtype == EC_BF16) {
-    // the W1/W3 product reads the kept rows of X itself (empty gather stage)
-    EC_HIP(mark(3, stream));
-    EC_HIP(ec::launch_gemm_w13_var(P.dtype, X, W1, W3, w.A, P.E, rows, rw.tiles13, rmax, rmax_e,
-                                   P.d, P.h, stream, w.sel));
-  } else {
-    EC_HIP(ec::launch_gather(P.dtype, X, w.sel, w.Xe, rmax, P.d, P.N, stream, rows + P.E));
-    EC_HIP(mark(3, stream));
-    EC_HIP(ec::launch_gemm_w13_var(P.dtype, w.Xe, W1, W3, w.A, P.E, rows, rw.tiles13, rmax,
-                                   rmax_e, P.d, P.h, stream));
-  }
+  // the W1/W3 product reads the kept rows of X itself (empty gather stage)
+  EC_HIP(mark(3, stream));
+  EC_HIP(ec::launch_gemm_w13_var(P.dtype, X, W1, W3, w.A, P.E, rows, rw.tiles13, rmax, rmax_e, P.d,
+                                 P.h, stream, w.sel));
   EC_HIP(mark(4, stream));
   EC_HIP(ec::launch_gemm_w2_var(P.dtype, w.A, W2, w.O, P.E, rows, rw.tiles2, rmax, rmax_e, P.d,
                                 P.h, stream));

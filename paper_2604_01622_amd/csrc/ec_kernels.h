@@ -28,11 +28,9 @@ hipError_t launch_router_softmax(int dtype, const void* X, const void* Wg, float
 hipError_t launch_topk(const float* ST, int N, int E, int K, const GroupTable& tab,
                        int32_t* sel_token, float* sel_gate, int32_t* slotT, hipStream_t st);
 
-// Xe[r, :] = X[sel_token[r], :] for all rows (with rows_dev: for r < *rows_dev,
-// rows being an upper bound).
+// Xe[r, :] = X[sel_token[r], :] for all rows.
 hipError_t launch_gather(int dtype, const void* X, const int32_t* sel_token, void* Xe,
-                         long rows, int d, int N, hipStream_t st,
-                         const int32_t* rows_dev = nullptr);
+                         long rows, int d, int N, hipStream_t st);
 
 // Y[i, :] = Xr[i, :] (if Xr) + sum_j S[i,j] O[j kstride + slotT[j,i], :] over experts j
 // with 0 <= slotT[j,i] < K (Xr may alias Y); kstride < 0 means K (one buffer of K
@@ -45,14 +43,14 @@ hipError_t launch_combine(int dtype, const void* O, const float* S, const int32_
 hipError_t launch_bwd_combine(int dtype, const void* dXe, const int32_t* slotT, const void* Xr,
                               void* dX, int N, int E, int K, int d, hipStream_t st);
 
-// Router backward, part 1: dZ = S * (dS - <S, dS>) / tau  [N,E] fp32, from
-// S_ij dS_ij = sum over q of dsp[(j K + slot_ij) nparts + q] on the selection
-// (0 elsewhere); dZb (optional) is a bf16 copy [N, EP] with zero columns E..EP-1.
-hipError_t launch_router_dz(const float* S, const float* dsp, int nparts, const int32_t* slotT,
-                            float* dZ, uint16_t* dZb, int N, int E, int EP, int K, float inv_tau,
-                            hipStream_t st);
+// Router backward, part 1: dZ = S * (dS - <S, dS>) / tau  [N, EP] in the storage type
+// (columns E..EP-1 zero), from S_ij dS_ij = sum over q of dsp[(j K + slot_ij) nparts + q]
+// on the selection (0 elsewhere).
+hipError_t launch_router_dz(int dtype, const float* S, const float* dsp, int nparts,
+                            const int32_t* slotT, void* dZ, int N, int E, int EP, int K,
+                            float inv_tau, hipStream_t st);
 
-// Router backward, part 2: dX = dZ Wg  (bf16: dZ is the padded bf16 copy).
+// Router backward, part 2: dX = dZ Wg.
 hipError_t launch_router_dx(int dtype, const void* dZ, const void* Wg, void* dX, int N, int E,
                             int EP, int d, hipStream_t st);
 
@@ -66,7 +64,7 @@ int router_dwg_splits(int N, int E, int d);
 
 // H = Xe W1^T, Xe W3^T -> A = SiLU(H1) * H3 (and H1, H3 if non-null).
 // `shared`: the same product for the shared experts (own kernel symbol).
-// rows (bf16 routed experts, may be null): Xe is then X itself and row m of
+// rows (routed experts, may be null): Xe is then X itself and row m of
 // expert e reads X[rows[e M + m]] (the gather happens in the operand load).
 // gate (may be null): [E, M] fp32, row m of expert e is written as
 // A = gate[e M + m] SiLU(H1) H3 (H1, H3 themselves unscaled).
@@ -82,7 +80,7 @@ hipError_t launch_gemm_w2(int dtype, const void* A, const void* W2, void* O, int
 // K-major.  dsp (may be null):
 // [E M, dsp_parts(dtype, h)] fp32, per row and column block the sum of dA * A
 // (A = SiLU(H1) H3), whose row sum is the gate's gradient times the gate when
-// dO holds the rows of dY.  rows (bf16, may be null): dO is then dY itself and
+// dO holds the rows of dY.  rows (may be null): dO is then dY itself and
 // row m of expert e reads dY[rows[e M + m]].
 hipError_t launch_gemm_dA(int dtype, const void* dO, const void* W2, const void* H1,
                           const void* H3, void* dH, int E, int M, int d, int h, hipStream_t st,
@@ -96,7 +94,7 @@ int dsp_parts(int dtype, int h);
 // The weights are read K-major (bf16: h a multiple of 64).
 hipError_t launch_gemm_dXe(int dtype, const void* dH, const void* W1, const void* W3, void* dXe,
                            int E, int M, int d, int h, hipStream_t st, bool shared = false);
-// dW2 = dO^T A  ([E,d,h]).  rows (bf16, may be null): dO is then dY itself and
+// dW2 = dO^T A  ([E,d,h]).  rows (may be null): dO is then dY itself and
 // row m of expert e reads dY[rows[e M + m]] (the gather happens in the loads).
 hipError_t launch_gemm_dW2(int dtype, const void* dO, const void* A, void* dW2, int E, int M,
                            int d, int h, hipStream_t st, const int32_t* rows = nullptr);
@@ -146,7 +144,7 @@ hipError_t launch_tc_offsets(const int32_t* cnt, int G, int E, int bm, int nt13,
 hipError_t launch_tc_place(int32_t* slotT, float* G, int N, int E, const GroupTable& tab, int g0,
                            const int32_t* seg, int32_t* sel, hipStream_t st);
 // The forward products over packed rows: expert e owns rows [rows[e], rows[e+1]).
-// sel (bf16, may be null): Xe is then X itself and packed row r reads X[sel[r]].
+// sel (may be null): Xe is then X itself and packed row r reads X[sel[r]].
 hipError_t launch_gemm_w13_var(int dtype, const void* Xe, const void* W1, const void* W3, void* A,
                                int E, const int32_t* rows, const int32_t* tiles, long max_rows,
                                int max_rows_per_expert, int d, int h, hipStream_t st,

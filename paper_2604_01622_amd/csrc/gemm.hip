@@ -27,7 +27,8 @@
 // row of their K-contiguous A, the dW2 and dW1/dW3 products per k row of their
 // K-major operand, so no gathered copy is ever written.
 //
-// fp32: a plain LDS-tiled FMA kernel with the same operand conventions.
+// fp32: gemm_f32_kernel, v_mfma_f32_32x32x2_f32 tiles with the same operand
+// conventions and gathers.
 #include <type_traits>
 
 #include "ec_common.h"
@@ -50,7 +51,7 @@ struct GemmParams {
   const void* A;
   long a_bs;
   int lda;
-  // bf16 K-contiguous A only (may be null): row m of batch e is row
+  // K-contiguous A only (may be null): row m of batch e is row
   // a_rows[e*a_rows_bs + r0 + m] of A itself (r0: the batch's first packed row
   // with var_rows, else 0), so the gather of the selected tokens happens in the
   // operand load
@@ -80,7 +81,7 @@ struct GemmParams {
   void* H3;
   long h_bs;
   int ldh;
-  // bf16 K-major operands (used with the OPT_GA / OPT_GB instantiations): row k
+  // K-major operands (used with the OPT_GA / OPT_GB instantiations): row k
   // of batch e's A is row ka_rows[e*k_rows_bs + k] of A itself (kb_rows: of
   // B), so the gather of the selected tokens happens in the operand load when
   // the contraction runs over an expert's rows
@@ -860,24 +861,49 @@ int fwd_block_rows(int M) {
   return r192 * 7 < r256 * 6 ? 192 : 256;
 }
 
-// ------------------------------------------------------------------ fp32 FMA
+// ------------------------------------------------------------------ fp32 MFMA
+//
+// v_mfma_f32_32x32x2_f32 over the same operand conventions: every product and sum in
+// fp32.  A k-step is 32 wide (128-byte rows, the layout and swizzle of the bf16
+// kernel's K-contiguous tiles); a lane's 16-byte chunk holds four consecutive k of its
+// row, MFMA i of a sub-step taking element i of both lane halves (k = 8 s + i and
+// 8 s + 4 + i).  K-major tiles stay K-major, read with four 4-byte reads per fragment.
+// The matrix cores bound it: a k-step of a 64 x 64 wave tile is 4096 MFMA cycles, far
+// more than its LDS reads (1/8 of the port) or its DMA, so one barrier per step and
+// two stages suffice, and accumulators go straight to memory (16 bytes a lane).
+// Measured, 16 experts x 512 rows, d 1024, h 512: W1/W3 484 -> 150 us (115 TFLOP/s, MFMA
+// busy 78% of the cycles), W2 240 -> 79, dA 268 -> 98, dX 530 -> 155, dW1/dW3 520 -> 158,
+// against a 64 x 64 tile of scalar FMAs; a plain 8192^3 library product reaches 154.
+constexpr int FK = 32;   // k-step
+// 128 x 128 tiles from one per CU on (the same problem in 64 x 64 tiles, whose waves
+// read a third more LDS per MFMA and meet at twice as many barriers: 1037 against 795 us
+// a training step); below that 64 x 64 tiles keep more CUs busy.
+constexpr long F32_BIG_TILES = 256;
 
-constexpr int FT = 64;   // tile
-constexpr int FK = 16;   // K step
+template <int BM, int BN, int WGM, int WGN, bool A_KC, bool B_KC, int EPI, int OPT>
+__global__ __launch_bounds__(64 * WGM * WGN) void gemm_f32_kernel(GemmParams p) {
+  constexpr int NT = 64 * WGM * WGN;
+  constexpr int WM = BM / WGM, WN = BN / WGN, MB = WM / 32, NB = WN / 32;
+  constexpr int A_BYTES = BM * FK * 4, STAGE_BYTES = (BM + BN) * FK * 4;
+  constexpr int AL = BM * 8 / NT, BL = BN * 8 / NT;   // 16-byte chunks per thread and step
+  static_assert(BM * 8 % NT == 0 && BN * 8 % NT == 0, "whole chunks per thread");
+  static_assert(EPI != EPI_SWIGLU || (B_KC && NB == 2), "a W1 and a W3 block per wave");
+  static_assert(EPI != EPI_SWIGLU_BWD || WN == 64, "a wave covers one 64-column partial");
+  constexpr bool GA = (OPT & OPT_GA) != 0;
+  static_assert(!(GA && A_KC) && (OPT & ~OPT_GA) == 0, "a K-major A may be gathered");
+  __shared__ __attribute__((aligned(1024))) char smem[2 * STAGE_BYTES];
 
-template <int EPI>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmParams p, int a_kc, int b_kc) {
-  __shared__ float sA[FK][FT + 1];
-  __shared__ float sB[FK][FT + 1];
-  __shared__ float sB3[FK][FT + 1];
-  const int e = blockIdx.z;
-  const int m0 = blockIdx.y * FT, n0 = blockIdx.x * FT;
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+  const int t = xcd_tile_id(blockIdx.x, gridDim.x);
+  const int per_b = p.MT * p.NT;
+  if (t >= p.batches * per_b) return;
+  const int e = t / per_b, rem = t - e * per_b;
+  const int m0 = rem % p.MT * BM;
+  const int n0 = rem / p.MT * (EPI == EPI_SWIGLU ? BN / 2 : BN);
   // rows of this batch: uniform (M), or [var_rows[e], var_rows[e+1]) of packed buffers
-  int M = p.M;
+  int M = p.M, row0 = 0;
   size_t a_off = (size_t)e * p.a_bs, c_off = (size_t)e * p.c_bs, h_off = (size_t)e * p.h_bs;
   if (p.var_rows) {
-    const int row0 = p.var_rows[e];
+    row0 = p.var_rows[e];
     M = p.var_rows[e + 1] - row0;
     a_off = (size_t)row0 * p.lda;
     c_off = (size_t)row0 * p.ldc;
@@ -887,98 +913,238 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmParams p, int a_kc, i
   const float* A = (const float*)p.A + a_off;
   const float* B = (const float*)p.B + (size_t)e * p.b_bs;
   const float* B2 = p.B2 ? (const float*)p.B2 + (size_t)e * p.b_bs : nullptr;
-  float acc[4][4] = {}, acc3[4][4] = {};
-  for (int k0 = 0; k0 < p.K; k0 += FK) {
-    for (int c = tid; c < FK * FT; c += 256) {
-      const int kk = c / FT, r = c % FT;
-      const int k = k0 + kk, m = m0 + r, n = n0 + r;
-      float va = 0.f, vb = 0.f, vb3 = 0.f;
-      if (k < p.kv_a && m < M) va = a_kc ? A[(size_t)m * p.lda + k] : A[(size_t)k * p.lda + m];
-      if (k < p.kv_b && n < p.N) {
-        if (b_kc) {
-          vb = B[(size_t)n * p.ldb + k];
-          if (EPI == EPI_SWIGLU) vb3 = B2[(size_t)n * p.ldb + k];
-        } else {
-          vb = (k < p.k_split) ? B[(size_t)k * p.ldb + n] : B2[(size_t)(k - p.k_split) * p.ldb + n];
-        }
-      }
-      sA[kk][r] = va;
-      sB[kk][r] = vb;
-      sB3[kk][r] = vb3;
+  const float* zero = reinterpret_cast<const float*>(g_zero_block);
+
+  const int tid = threadIdx.x, lane = tid & 63, l31 = lane & 31, half = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave % WGM, wn = wave / WGM;
+
+  // DMA sources: load q of a thread fills the 16 bytes at (wave L + q) 1024 + 16 lane
+  // of the operand's area.  K-contiguous: the chunk's address at k-step 0.  K-major: the
+  // chunk's column; its row is formed per step (a gathered row's index is read a
+  // step ahead); rows past the valid K and columns past the width read zeros.
+  const float* a_src[AL];
+  const float* b_src[BL];
+  int a_idx[AL];
+  auto km_idx = [&](int k) -> int {
+    return p.ka_rows[(size_t)e * p.k_rows_bs + (k < p.kv_a ? k : p.kv_a - 1)];
+  };
+#pragma unroll
+  for (int q = 0; q < AL; ++q) {
+    const int id = (wave * AL + q) * 64 + lane;
+    if constexpr (A_KC) {
+      const int row = id >> 3, lc = (id & 7) ^ kc_swz<64>(row);
+      int r = m0 + row;
+      r = r < M ? r : M - 1;
+      a_src[q] = p.a_rows ? (const float*)p.A +
+                                (size_t)p.a_rows[(size_t)e * p.a_rows_bs + row0 + r] * p.lda + lc * 4
+                          : A + (size_t)r * p.lda + lc * 4;
+    } else {
+      const int col = m0 + id % (BM / 4) * 4;
+      a_src[q] = col < M ? (GA ? (const float*)p.A : A) + col : nullptr;
+      if constexpr (GA) a_idx[q] = p.kv_a > 0 ? km_idx(id / (BM / 4)) : 0;
     }
-    __syncthreads();
+  }
 #pragma unroll
-    for (int kk = 0; kk < FK; ++kk) {
-      float a[4], b[4], b3[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        a[i] = sA[kk][ty * 4 + i];
-        b[i] = sB[kk][tx * 4 + i];
-        b3[i] = sB3[kk][tx * 4 + i];
+  for (int q = 0; q < BL; ++q) {
+    const int id = (wave * BL + q) * 64 + lane;
+    if constexpr (B_KC) {
+      const int row = id >> 3, lc = (id & 7) ^ kc_swz<64>(row);
+      if constexpr (EPI == EPI_SWIGLU) {
+        int r = n0 + row % (BN / 2);
+        r = r < p.N ? r : p.N - 1;
+        b_src[q] = (row < BN / 2 ? B : B2) + (size_t)r * p.ldb + lc * 4;
+      } else {
+        int r = n0 + row;
+        r = r < p.N ? r : p.N - 1;
+        b_src[q] = B + (size_t)r * p.ldb + lc * 4;
       }
+    } else {
+      const int col = n0 + id % (BN / 4) * 4;
+      b_src[q] = col < p.N ? B + col : nullptr;
+    }
+  }
+  const long b2_off = B2 ? B2 - B : 0;
+  auto issue = [&](int kt, int stage) {
+    char* base = smem + stage * STAGE_BYTES;
+#pragma unroll
+    for (int q = 0; q < AL; ++q) {
+      const float* g;
+      if constexpr (A_KC) {
+        g = a_src[q] + kt * FK;
+      } else {
+        const int k = kt * FK + ((wave * AL + q) * 64 + lane) / (BM / 4);
+        g = (k < p.kv_a && a_src[q]) ? a_src[q] + (size_t)(GA ? a_idx[q] : k) * p.lda : zero;
+        if constexpr (GA) a_idx[q] = km_idx(k + FK);
+      }
+      dma16(g, base + (wave * AL + q) * 1024);
+    }
+#pragma unroll
+    for (int q = 0; q < BL; ++q) {
+      const float* g;
+      if constexpr (B_KC) {
+        g = b_src[q] + kt * FK;
+      } else {
+        const int k = kt * FK + ((wave * BL + q) * 64 + lane) / (BN / 4);
+        const float* s = b_src[q] + (k < p.k_split ? 0 : b2_off);
+        const int kr = k < p.k_split ? k : k - p.k_split;
+        g = (k < p.kv_b && b_src[q]) ? s + (size_t)kr * p.ldb : zero;
+      }
+      dma16(g, base + A_BYTES + (wave * BL + q) * 1024);
+    }
+  };
+  // the four k of sub-step s that this lane holds, for tile row (or column) base + lane % 32
+  auto frag = [&](const char* __restrict__ tile, auto kc, int width, int base, int s) -> f32x4 {
+    if constexpr (decltype(kc)::value) {
+      const int row = base + l31;
+      return *reinterpret_cast<const f32x4*>(tile + row * (FK * 4) +
+                                             (((2 * s + half) ^ kc_swz<64>(row)) << 4));
+    } else {
+      const float* c = reinterpret_cast<const float*>(tile) + (8 * s + 4 * half) * width + base + l31;
+      return f32x4{c[0], c[width], c[2 * width], c[3 * width]};
+    }
+  };
+  auto b_col = [&](int ni) -> int {
+    return EPI == EPI_SWIGLU ? ni * (BN / 2) + wn * (WN / 2) : wn * WN + ni * 32;
+  };
+
+  f32x16 acc[MB][NB];
+#pragma unroll
+  for (int mi = 0; mi < MB; ++mi)
+#pragma unroll
+    for (int ni = 0; ni < NB; ++ni)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[mi][ni][r] = 0.f;
+
+  const int KT = (p.K + FK - 1) / FK;
+  if (KT > 0) issue(0, 0);
+  for (int kt = 0; kt < KT; ++kt) {
+    // step kt has landed for every wave, and every wave has read step kt - 1
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+    __syncthreads();
+    if (kt + 1 < KT) issue(kt + 1, (kt + 1) & 1);
+    const char* sa = smem + (kt & 1) * STAGE_BYTES;
+    const char* sb = sa + A_BYTES;
+    // the fragments of sub-step s + 1 are requested before the MFMAs of sub-step s
+    f32x4 af[2][MB], bf[2][NB];
+    auto load = [&](int s) {
+#pragma unroll
+      for (int mi = 0; mi < MB; ++mi)
+        af[s & 1][mi] = frag(sa, std::integral_constant<bool, A_KC>{}, BM, wm * WM + mi * 32, s);
+#pragma unroll
+      for (int ni = 0; ni < NB; ++ni)
+        bf[s & 1][ni] = frag(sb, std::integral_constant<bool, B_KC>{}, BN, b_col(ni), s);
+    };
+    load(0);
+#pragma unroll
+    for (int s = 0; s < FK / 8; ++s) {
+      if (s + 1 < FK / 8) load(s + 1);
+      __builtin_amdgcn_sched_barrier(0);
+      // B first: each lane ends with four consecutive output columns of a row
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-          acc[i][jj] = fmaf(a[i], b[jj], acc[i][jj]);
-          if (EPI == EPI_SWIGLU) acc3[i][jj] = fmaf(a[i], b3[jj], acc3[i][jj]);
-        }
+        for (int mi = 0; mi < MB; ++mi)
+#pragma unroll
+          for (int ni = 0; ni < NB; ++ni)
+            acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(
+                bf[s & 1][ni][i], af[s & 1][mi][i], acc[mi][ni], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    __syncthreads();
   }
-  float dsum[4] = {0.f, 0.f, 0.f, 0.f};   // SwiGLU backward: gate-gradient partials per row
+
+  // acc[mi][ni][4 g + i]: row lane % 32 of the block, column 8 g + 4 (lane / 32) + i
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int mi = 0; mi < MB; ++mi) {
+    const int m = m0 + wm * WM + mi * 32 + l31;
+    const bool row_ok = m < M;
+    const float gate =
+        ((EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_BWD) && p.gate && row_ok)
+            ? p.gate[(size_t)e * p.gate_bs + m] : 1.f;
+    float dsum = 0.f;   // SwiGLU backward: the row's gate-gradient partial
 #pragma unroll
-    for (int jj = 0; jj < 4; ++jj) {
-      const int m = m0 + ty * 4 + i, n = n0 + tx * 4 + jj;
-      if (m >= M || n >= p.N) continue;
-      if (EPI == EPI_STORE || EPI == EPI_STORE_ADD) {
-        const bool second = m >= p.c_split;
-        const int mm = second ? m - p.c_split : m;
-        float* dst = (float*)(second ? p.C2 : p.C) + c_off + (size_t)mm * p.ldc + n;
-        *dst = (EPI == EPI_STORE_ADD) ? *dst + acc[i][jj] : acc[i][jj];
-      } else if (EPI == EPI_SWIGLU) {
-        const float h1 = acc[i][jj], h3 = acc3[i][jj];
-        const float g = p.gate ? p.gate[(size_t)e * p.gate_bs + m] : 1.f;
-        ((float*)p.C)[c_off + (size_t)m * p.ldc + n] = silu_f(h1) * h3 * g;
-        if (p.H1) {
+    for (int ni = 0; ni < (EPI == EPI_SWIGLU ? 1 : NB); ++ni) {
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int n = n0 + (EPI == EPI_SWIGLU ? wn * (WN / 2) : wn * WN + ni * 32) + 8 * g + 4 * half;
+        if (!row_ok || n >= p.N) continue;
+        float v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = acc[mi][ni][4 * g + i];
+        if constexpr (EPI == EPI_STORE || EPI == EPI_STORE_ADD) {
+          const bool second = m >= p.c_split;
+          float4* dst = reinterpret_cast<float4*>((float*)(second ? p.C2 : p.C) + c_off +
+                                                  (size_t)(second ? m - p.c_split : m) * p.ldc + n);
+          float4 o = make_float4(v[0], v[1], v[2], v[3]);
+          if constexpr (EPI == EPI_STORE_ADD) {
+            const float4 old = *dst;
+            o = make_float4(old.x + o.x, old.y + o.y, old.z + o.z, old.w + o.w);
+          }
+          *dst = o;
+        } else if constexpr (EPI == EPI_SWIGLU) {
+          float a[4], h3[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            h3[i] = acc[mi][NB - 1][4 * g + i];
+            a[i] = silu_f(v[i]) * h3[i] * gate;
+          }
+          *reinterpret_cast<float4*>((float*)p.C + c_off + (size_t)m * p.ldc + n) =
+              make_float4(a[0], a[1], a[2], a[3]);
+          if (p.H1) {
+            const size_t ho = h_off + (size_t)m * p.ldh + n;
+            *reinterpret_cast<float4*>((float*)p.H1 + ho) = make_float4(v[0], v[1], v[2], v[3]);
+            *reinterpret_cast<float4*>((float*)p.H3 + ho) = make_float4(h3[0], h3[1], h3[2], h3[3]);
+          }
+        } else {
           const size_t ho = h_off + (size_t)m * p.ldh + n;
-          ((float*)p.H1)[ho] = h1;
-          ((float*)p.H3)[ho] = h3;
+          const float4 h1v = *reinterpret_cast<const float4*>((const float*)p.H1 + ho);
+          const float4 h3v = *reinterpret_cast<const float4*>((const float*)p.H3 + ho);
+          const float h1a[4] = {h1v.x, h1v.y, h1v.z, h1v.w}, h3a[4] = {h3v.x, h3v.y, h3v.z, h3v.w};
+          float d1[4], d3[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float da = v[i] * gate, sg = sigmoid_f(h1a[i]);
+            d1[i] = da * h3a[i] * sg * (1.0f + h1a[i] * (1.0f - sg));
+            d3[i] = da * h1a[i] * sg;
+            dsum = fmaf(da, h1a[i] * sg * h3a[i], dsum);
+          }
+          const size_t off = c_off + (size_t)m * p.ldc + n;
+          *reinterpret_cast<float4*>((float*)p.C + off) = make_float4(d1[0], d1[1], d1[2], d1[3]);
+          *reinterpret_cast<float4*>((float*)p.C2 + off) = make_float4(d3[0], d3[1], d3[2], d3[3]);
         }
-      } else {
-        const size_t ho = h_off + (size_t)m * p.ldh + n;
-        const float h1 = ((const float*)p.H1)[ho], h3 = ((const float*)p.H3)[ho];
-        const float da = acc[i][jj] * (p.gate ? p.gate[(size_t)e * p.gate_bs + m] : 1.f);
-        const float sg = sigmoid_f(h1);
-        const size_t off = c_off + (size_t)m * p.ldc + n;
-        ((float*)p.C)[off] = da * h3 * sg * (1.0f + h1 * (1.0f - sg));
-        ((float*)p.C2)[off] = da * h1 * sg;
-        dsum[i] = fmaf(da, h1 * sg * h3, dsum[i]);
       }
     }
-  if (EPI == EPI_SWIGLU_BWD && p.dsp) {
-    // the 16 threads of a row (tx, consecutive lanes) hold its 64 columns
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      float t = dsum[i];
-      t += __shfl_xor(t, 1, 64);
-      t += __shfl_xor(t, 2, 64);
-      t += __shfl_xor(t, 4, 64);
-      t += __shfl_xor(t, 8, 64);
-      const int m = m0 + ty * 4 + i;
-      if (tx == 0 && m < M) p.dsp[((size_t)e * p.M + m) * p.dsp_ld + blockIdx.x] = t;
+    if constexpr (EPI == EPI_SWIGLU_BWD) {
+      // the two lanes of a row hold its 64-column block (N is a multiple of 64)
+      const float tsum = dsum + __shfl_xor(dsum, 32, 64);
+      const int nb = n0 + wn * WN;
+      if (p.dsp && half == 0 && row_ok && nb < p.N)
+        p.dsp[((size_t)e * p.M + m) * p.dsp_ld + (nb >> 6)] = tsum;
     }
   }
 }
 
-template <int EPI>
-hipError_t run_f32(GemmParams p, int a_kc, int b_kc, hipStream_t st) {
-  if (p.batches == 0 || p.M == 0 || p.N == 0) return hipSuccess;
-  const dim3 grid((p.N + FT - 1) / FT, (p.M + FT - 1) / FT, p.batches);
-  gemm_f32_kernel<EPI><<<grid, 256, 0, st>>>(p, a_kc, b_kc);
+template <int BM, int BN, int WGM, int WGN, bool A_KC, bool B_KC, int EPI, int OPT>
+hipError_t launch_f32_tile(GemmParams p, hipStream_t st) {
+  p.MT = (p.M + BM - 1) / BM;
+  p.NT = (EPI == EPI_SWIGLU) ? (p.N + BN / 2 - 1) / (BN / 2) : (p.N + BN - 1) / BN;
+  const long ntile = (long)p.batches * p.MT * p.NT;
+  if (ntile == 0) return hipSuccess;
+  if (ntile >= (1l << 31) - 8) return hipErrorInvalidValue;
+  const long grid = (ntile + 7) / 8 * 8;
+  gemm_f32_kernel<BM, BN, WGM, WGN, A_KC, B_KC, EPI, OPT>
+      <<<dim3((unsigned)grid), 64 * WGM * WGN, 0, st>>>(p);
   return hipGetLastError();
+}
+
+// OPT: as in run_dma.
+template <bool A_KC, bool B_KC, int EPI, int OPT = 0>
+hipError_t run_f32(const GemmParams& p, hipStream_t st) {
+  if (((OPT & OPT_GA) != 0) != (p.ka_rows != nullptr)) return hipErrorInvalidValue;
+  const int nw = EPI == EPI_SWIGLU ? 2 * p.N : p.N;
+  const long big = (long)p.batches * ((p.M + 127) / 128) * ((nw + 127) / 128);
+  if (big >= F32_BIG_TILES) return launch_f32_tile<128, 128, 2, 2, A_KC, B_KC, EPI, OPT>(p, st);
+  return launch_f32_tile<64, 64, 2, 1, A_KC, B_KC, EPI, OPT>(p, st);
 }
 
 GemmParams base_params() {
@@ -1035,8 +1201,7 @@ hipError_t launch_gemm_w13(int dtype, const void* Xe, const void* W1, const void
   p.H1 = H1; p.H3 = H3; p.h_bs = (long)M * h; p.ldh = h;
   if (M == 0) return hipSuccess;
   if (dtype == DT_F32) {
-    if (rows) return hipErrorInvalidValue;   // fp32 reads a gathered Xe
-    return run_f32<EPI_SWIGLU>(p, 1, 1, st);
+    return run_f32<true, true, EPI_SWIGLU>(p, st);
   }
   if (shared) {
     if (rows) return hipErrorInvalidValue;   // the shared experts read X as is
@@ -1057,7 +1222,7 @@ hipError_t launch_gemm_w2(int dtype, const void* A, const void* W2, void* O, int
   p.M = M; p.N = d; p.K = h; p.kv_a = h; p.kv_b = h; p.batches = E;
   p.C = O; p.c_bs = (long)M * d; p.ldc = d;
   if (M == 0) return hipSuccess;
-  if (dtype == DT_F32) return run_f32<EPI_STORE>(p, 1, 1, st);
+  if (dtype == DT_F32) return run_f32<true, true, EPI_STORE>(p, st);
   if (shared) return run_dma<256, 256, 4, 2, 64, 2, true, true, EPI_STORE, false, G_SH_W2>(p, st);
   switch (fwd_block_rows(M)) {
     case 128: return run_dma<128, 256, 2, 4, 64, 2, true, true, EPI_STORE, false, G_W2>(p, st);
@@ -1084,8 +1249,7 @@ hipError_t launch_gemm_dA(int dtype, const void* dO, const void* W2, const void*
   p.dsp = dsp; p.dsp_ld = dsp_parts(dtype, h);
   if (M == 0) return hipSuccess;
   if (dtype == DT_F32) {
-    if (rows) return hipErrorInvalidValue;   // fp32 reads a gathered dO
-    return run_f32<EPI_SWIGLU_BWD>(p, 1, 0, st);
+    return run_f32<true, false, EPI_SWIGLU_BWD>(p, st);
   }
   if (shared && rows) return hipErrorInvalidValue;
   // B = W2 K-major: B(n, k) = W2[k, n]
@@ -1103,8 +1267,8 @@ hipError_t launch_gemm_dXe(int dtype, const void* dH, const void* W1, const void
   p.M = M; p.N = d; p.K = 2 * h; p.kv_a = 2 * h; p.kv_b = 2 * h; p.batches = E;
   p.C = dXe; p.c_bs = (long)M * d; p.ldc = d;
   if (M == 0) return hipSuccess;
-  if (dtype == DT_F32) return shared ? run_f32<EPI_STORE_ADD>(p, 1, 0, st)
-                                     : run_f32<EPI_STORE>(p, 1, 0, st);
+  if (dtype == DT_F32) return shared ? run_f32<true, false, EPI_STORE_ADD>(p, st)
+                                     : run_f32<true, false, EPI_STORE>(p, st);
   // bf16: B K-major, rows k >= h from W3 (h is a multiple of the k-step); the
   // shared experts' input gradient is added to dX
   if (h % 64 != 0) return hipErrorInvalidValue;
@@ -1122,11 +1286,11 @@ hipError_t launch_gemm_dW2(int dtype, const void* dO, const void* A, void* dW2, 
   p.M = d; p.N = h; p.K = M; p.kv_a = M; p.kv_b = M; p.batches = E;
   p.C = dW2; p.c_bs = (long)d * h; p.ldc = h;
   if (rows) {   // dO is dY itself, row k of expert e is dY[rows[e M + k]]
-    if (dtype == DT_F32) return hipErrorInvalidValue;
     p.a_bs = 0; p.ka_rows = rows; p.k_rows_bs = M;
+    if (dtype == DT_F32) return run_f32<false, false, EPI_STORE, OPT_GA>(p, st);
     return run_dma<256, 256, 4, 2, 64, 2, false, false, EPI_STORE, false, G_DW2, OPT_GA>(p, st);
   }
-  if (dtype == DT_F32) return run_f32<EPI_STORE>(p, 0, 0, st);
+  if (dtype == DT_F32) return run_f32<false, false, EPI_STORE>(p, st);
   return run_dma<256, 256, 4, 2, 64, 2, false, false, EPI_STORE, false, G_DW2>(p, st);
 }
 
@@ -1139,24 +1303,24 @@ hipError_t launch_gemm_dW13(int dtype, const void* dH, const void* Xe, void* dW1
   p.M = 2 * h; p.N = d; p.K = M; p.kv_a = M; p.kv_b = M; p.batches = E;
   p.C = dW1; p.C2 = dW3; p.c_split = h; p.c_bs = (long)h * d; p.ldc = d;
   if (rows) {   // Xe is X itself, row k of expert e is X[rows[e M + k]]
-    if (dtype == DT_F32) return hipErrorInvalidValue;
+    if (dtype == DT_F32) return hipErrorInvalidValue;   // fp32 reads the saved Xe
     p.b_bs = 0; p.kb_rows = rows; p.k_rows_bs = M;
     return run_dma<256, 256, 4, 2, 64, 2, false, false, EPI_STORE, false, G_DW13, OPT_GB>(p, st);
   }
-  if (dtype == DT_F32) return run_f32<EPI_STORE>(p, 0, 0, st);
+  if (dtype == DT_F32) return run_f32<false, false, EPI_STORE>(p, st);
   return run_dma<256, 256, 4, 2, 64, 2, false, false, EPI_STORE, false, G_DW13>(p, st);
 }
 
 hipError_t launch_router_dx(int dtype, const void* dZ, const void* Wg, void* dX, int N, int E,
                             int EP, int d, hipStream_t st) {
-  // dX[i, n] = sum_j dZ[i, j] Wg[j, n]; dZ is [N, EP] (bf16, zero padded) or [N, E] fp32
+  // dX[i, n] = sum_j dZ[i, j] Wg[j, n]; dZ is [N, EP], zero padded
   GemmParams p = base_params();
-  p.A = dZ; p.a_bs = 0; p.lda = (dtype == DT_F32) ? E : EP;
+  p.A = dZ; p.a_bs = 0; p.lda = EP;
   p.B = Wg; p.b_bs = 0; p.ldb = d;
-  p.M = N; p.N = d; p.K = (dtype == DT_F32) ? E : EP; p.kv_a = p.K; p.kv_b = E; p.batches = 1;
+  p.M = N; p.N = d; p.K = EP; p.kv_a = EP; p.kv_b = E; p.batches = 1;
   p.C = dX; p.c_bs = 0; p.ldc = d;
   if (N == 0) return hipSuccess;
-  if (dtype == DT_F32) return run_f32<EPI_STORE>(p, 1, 0, st);
+  if (dtype == DT_F32) return run_f32<true, false, EPI_STORE>(p, st);
   return run_dma<256, 256, 4, 2, 64, 2, true, false, EPI_STORE, false, G_ROUTER_DX>(p, st);
 }
 
@@ -1175,23 +1339,21 @@ hipError_t launch_router_dwg(int dtype, const void* dZ, const void* X, float* dW
   if (N == 0 || splits < 1) return launch_zero(dWg, (size_t)E * d * sizeof(float), st);
   const int chunk = (N + splits - 1) / splits;
   GemmParams p = base_params();
-  const size_t xs = dtype == DT_F32 ? 4 : 2;
-  p.A = dZ; p.a_bs = (long)chunk * ((dtype == DT_F32) ? E : EP); p.lda = (dtype == DT_F32) ? E : EP;
+  p.A = dZ; p.a_bs = (long)chunk * EP; p.lda = EP;
   p.B = X; p.b_bs = (long)chunk * d; p.ldb = d;
   p.M = E; p.N = d; p.K = chunk; p.batches = splits;
   p.C = part; p.c_bs = (long)E * d; p.ldc = d;
-  (void)xs;
   // each split sees rows [s*chunk, min(N, (s+1)*chunk)); the last may be short
   const int last = N - (splits - 1) * chunk;
   hipError_t err;
   if (last == chunk) {
     p.kv_a = chunk; p.kv_b = chunk;
-    if (dtype == DT_F32) err = run_f32<EPI_STORE>(p, 0, 0, st);
+    if (dtype == DT_F32) err = run_f32<false, false, EPI_STORE>(p, st);
     else err = run_dma<128, 256, 2, 4, 64, 2, false, false, EPI_STORE, true, G_ROUTER_DWG>(p, st);
   } else {
     GemmParams p1 = p;
     p1.batches = splits - 1; p1.kv_a = chunk; p1.kv_b = chunk;
-    err = (splits > 1) ? ((dtype == DT_F32) ? run_f32<EPI_STORE>(p1, 0, 0, st)
+    err = (splits > 1) ? ((dtype == DT_F32) ? run_f32<false, false, EPI_STORE>(p1, st)
                                             : run_dma<128, 256, 2, 4, 64, 2, false, false, EPI_STORE, true, G_ROUTER_DWG>(p1, st))
                        : hipSuccess;
     if (err != hipSuccess) return err;
@@ -1201,7 +1363,7 @@ hipError_t launch_router_dwg(int dtype, const void* dZ, const void* X, float* dW
     p2.B = (const char*)p.B + bo * ((dtype == DT_F32) ? 4 : 2);
     p2.C = part + (size_t)(splits - 1) * E * d;
     p2.batches = 1; p2.kv_a = last; p2.kv_b = last;
-    err = (dtype == DT_F32) ? run_f32<EPI_STORE>(p2, 0, 0, st)
+    err = (dtype == DT_F32) ? run_f32<false, false, EPI_STORE>(p2, st)
                             : run_dma<128, 256, 2, 4, 64, 2, false, false, EPI_STORE, true, G_ROUTER_DWG>(p2, st);
   }
   if (err != hipSuccess) return err;
@@ -1290,7 +1452,6 @@ hipError_t launch_gemm_w13_var(int dtype, const void* Xe, const void* W1, const 
   GemmParams p = base_params();
   p.A = Xe; p.lda = d;
   if (sel) {   // Xe is X itself, packed row r is X[sel[r]]
-    if (dtype == DT_F32) return hipErrorInvalidValue;
     p.a_rows = sel; p.a_rows_bs = 0;
   }
   p.B = W1; p.B2 = W3; p.b_bs = (long)h * d; p.ldb = d;
@@ -1298,7 +1459,7 @@ hipError_t launch_gemm_w13_var(int dtype, const void* Xe, const void* W1, const 
   p.C = A; p.ldc = h; p.ldh = h;
   p.var_rows = rows; p.var_tiles = tiles;
   if (max_rows == 0) return hipSuccess;
-  if (dtype == DT_F32) return run_f32<EPI_SWIGLU>(p, 1, 1, st);
+  if (dtype == DT_F32) return run_f32<true, true, EPI_SWIGLU>(p, st);
   return run_dma_var<256, 256, 2, 4, 64, 2, true, true, EPI_SWIGLU, false, G_TC_W13>(p, max_rows,
                                                                                      st);
 }
@@ -1313,7 +1474,7 @@ hipError_t launch_gemm_w2_var(int dtype, const void* A, const void* W2, void* O,
   p.C = O; p.ldc = d;
   p.var_rows = rows; p.var_tiles = tiles;
   if (max_rows == 0) return hipSuccess;
-  if (dtype == DT_F32) return run_f32<EPI_STORE>(p, 1, 1, st);
+  if (dtype == DT_F32) return run_f32<true, true, EPI_STORE>(p, st);
   return run_dma_var<256, 256, 4, 2, 64, 2, true, true, EPI_STORE, false, G_TC_W2>(p, max_rows,
                                                                                    st);
 }

@@ -13,16 +13,13 @@ namespace {
 // ---------------------------------------------------------------- gather
 // One wave per expert row; 16-byte vectors, all loads of a row issued before
 // its stores.
-// With rows_dev the row count is read from device memory (rows is then the
-// launch's upper bound).
 template <int U>
 __global__ __launch_bounds__(256) void gather_kernel(const uint4* __restrict__ X,
                                                      const int32_t* __restrict__ sel,
                                                      uint4* __restrict__ Xe, long rows, int vpr,
-                                                     int N, const int32_t* rows_dev) {
+                                                     int N) {
   const int lane = threadIdx.x & 63;
   const long r = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (rows_dev && r >= *rows_dev) return;
   if (r >= rows) return;
   const int i = sel[r];
   if ((unsigned)i >= (unsigned)N) return;  // never for a valid selection
@@ -176,8 +173,8 @@ hipError_t run_combine(const T* Src, const float* S, const int32_t* slotT, const
 // dZ[i, :] = S_i * (dS_i - <S_i, dS_i>) / tau = (u_i - S_i sum_j u_ij) / tau with
 // u_ij = S_ij dS_ij: on the selection the sum of the dA product's partials of
 // row (j, slot_ij) (they carry the gate: dA = S_ij dY_i W2), 0 off it; dS
-// itself is never formed.  Writes fp32 dZ [N, E] and, if dZb is given,
-// a bf16 copy [N, EP] whose columns E..EP-1 are zero.  A workgroup stages a
+// itself is never formed.  Writes dZ [N, EP] in the storage type (columns E..EP-1
+// are zero), the operand of the router's two gradient products.  A workgroup stages a
 // tile of `tok` (<= RZ_TOK) tokens through LDS so that every global access is
 // coalesced; the tile keeps the dynamic LDS under 64 KiB for any E <= 256.
 constexpr int RZ_TOK = 32;
@@ -188,13 +185,12 @@ constexpr int RZ_B = 8;       // (expert, token) entries per thread per batch
 // batch first loads the slots of its RZ_B entries, then every partial they
 // select, so the loads are in flight together; the partials of a row are then
 // added in a fixed order (0, 1, ...).
-template <int NP>
+template <int NP, typename T>
 __global__ __launch_bounds__(256) void router_dz_kernel(const float* __restrict__ S,
                                                         const float* __restrict__ dsp,
                                                         int nparts,
                                                         const int32_t* __restrict__ slotT,
-                                                        float* __restrict__ dZ,
-                                                        bf16_t* __restrict__ dZb, int N, int E,
+                                                        T* __restrict__ dZ, int N, int E,
                                                         int EP, int K, float inv_tau, int tok) {
   extern __shared__ float rz_lds[];
   const int LD = E + 1;
@@ -283,16 +279,10 @@ __global__ __launch_bounds__(256) void router_dz_kernel(const float* __restrict_
     if (lane == 0) sdot[t] = v;
   }
   __syncthreads();
-  for (int c = tid; c < nt * E; c += 256) {
-    const int t = c / E, j = c % E;
-    dZ[(size_t)i0 * E + c] = (sU[t * LD + j] - sS[t * LD + j] * sdot[t]) * inv_tau;
-  }
-  if (dZb) {
-    for (int c = tid; c < nt * EP; c += 256) {
-      const int t = c / EP, j = c % EP;
-      const float z = (j < E) ? (sU[t * LD + j] - sS[t * LD + j] * sdot[t]) * inv_tau : 0.f;
-      dZb[(size_t)i0 * EP + c] = (bf16_t)f32_to_bf16(z);
-    }
+  for (int c = tid; c < nt * EP; c += 256) {
+    const int t = c / EP, j = c % EP;
+    const float z = (j < E) ? (sU[t * LD + j] - sS[t * LD + j] * sdot[t]) * inv_tau : 0.f;
+    Elem<T>::store1(dZ + (size_t)i0 * EP + c, z);
   }
 }
 
@@ -335,12 +325,12 @@ __global__ void zero_kernel(uint4* p, size_t n16, unsigned char* tail, size_t nt
 }  // namespace
 
 hipError_t launch_gather(int dtype, const void* X, const int32_t* sel_token, void* Xe, long rows,
-                         int d, int N, hipStream_t st, const int32_t* rows_dev) {
+                         int d, int N, hipStream_t st) {
   if (rows == 0) return hipSuccess;
   const int vpr = d * (dtype == DT_F32 ? 4 : 2) / 16;
   const long grid = (rows + 3) / 4;
   gather_kernel<4><<<dim3((unsigned)grid), 256, 0, st>>>((const uint4*)X, sel_token, (uint4*)Xe,
-                                                         rows, vpr, N, rows_dev);
+                                                         rows, vpr, N);
   return hipGetLastError();
 }
 
@@ -366,31 +356,36 @@ hipError_t launch_bwd_combine(int dtype, const void* dXe, const int32_t* slotT, 
                                    (bf16_t*)dX, N, E, K, d, st, K);
 }
 
-hipError_t launch_router_dz(const float* S, const float* dsp, int nparts, const int32_t* slotT,
-                            float* dZ, uint16_t* dZb, int N, int E, int EP, int K, float inv_tau,
-                            hipStream_t st) {
-  if (N == 0) return hipSuccess;
+namespace {
+
+template <int NP>
+hipError_t run_router_dz(int dtype, const float* S, const float* dsp, int nparts,
+                         const int32_t* slotT, void* dZ, int N, int E, int EP, int K,
+                         float inv_tau, hipStream_t st) {
   const int tok = E > 128 ? RZ_TOK / 2 : RZ_TOK;
   const size_t lds = (size_t)2 * tok * (E + 1) * sizeof(float);
   const int grid = (N + tok - 1) / tok;
-  switch (nparts) {
-    case 4:
-      router_dz_kernel<4><<<grid, 256, lds, st>>>(S, dsp, nparts, slotT, dZ, dZb, N, E, EP, K,
-                                                  inv_tau, tok);
-      break;
-    case 8:
-      router_dz_kernel<8><<<grid, 256, lds, st>>>(S, dsp, nparts, slotT, dZ, dZb, N, E, EP, K,
-                                                  inv_tau, tok);
-      break;
-    case 16:
-      router_dz_kernel<16><<<grid, 256, lds, st>>>(S, dsp, nparts, slotT, dZ, dZb, N, E, EP, K,
-                                                   inv_tau, tok);
-      break;
-    default:
-      router_dz_kernel<0><<<grid, 256, lds, st>>>(S, dsp, nparts, slotT, dZ, dZb, N, E, EP, K,
-                                                  inv_tau, tok);
-  }
+  if (dtype == DT_F32)
+    router_dz_kernel<NP, float><<<grid, 256, lds, st>>>(S, dsp, nparts, slotT, (float*)dZ, N, E, EP,
+                                                        K, inv_tau, tok);
+  else
+    router_dz_kernel<NP, bf16_t><<<grid, 256, lds, st>>>(S, dsp, nparts, slotT, (bf16_t*)dZ, N, E,
+                                                         EP, K, inv_tau, tok);
   return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_router_dz(int dtype, const float* S, const float* dsp, int nparts,
+                            const int32_t* slotT, void* dZ, int N, int E, int EP, int K,
+                            float inv_tau, hipStream_t st) {
+  if (N == 0) return hipSuccess;
+  switch (nparts) {
+    case 4: return run_router_dz<4>(dtype, S, dsp, nparts, slotT, dZ, N, E, EP, K, inv_tau, st);
+    case 8: return run_router_dz<8>(dtype, S, dsp, nparts, slotT, dZ, N, E, EP, K, inv_tau, st);
+    case 16: return run_router_dz<16>(dtype, S, dsp, nparts, slotT, dZ, N, E, EP, K, inv_tau, st);
+    default: return run_router_dz<0>(dtype, S, dsp, nparts, slotT, dZ, N, E, EP, K, inv_tau, st);
+  }
 }
 
 hipError_t launch_coverage_count(const int32_t* slotT, int N, int E, int32_t* cnt,

@@ -260,6 +260,29 @@ def test_near_the_size_limit():
     assert all(v <= out_tol("bf16") for v in errs.values()), errs
 
 
+@pytest.mark.parametrize("lens,d,E,h,cf", [
+    ([65], 64, 5, 64, 2.0),             # 64-wide tiles, one of them nearly empty
+    ([257], 192, 17, 320, 3.0),         # ... column blocks past the width
+    ([1029, 515], 448, 48, 192, 8.0),   # 128-wide tiles, ragged rows and half-empty columns
+])
+def test_f32_product_tiles(lens, d, E, h, cf):
+    wl = synth.small("f32tiles", lens, d, E, h, dtype="f32", seed=44, capacity_factor=cf,
+                     backward=True, d_shared=64)
+    full_case(wl)
+
+
+@pytest.mark.parametrize("lens,d,E", [
+    ([9], 64, 1),              # less than one K tile, one token past a workgroup
+    ([130], 320, 33),          # K tiles of 64 with 33 experts
+    ([77], 448, 129),          # K tiles of 32
+    ([16380, 9], 192, 7),      # 32 tokens per workgroup, a partial K tile, a ragged end
+])
+def test_f32_router_tiles(lens, d, E):
+    wl = synth.small("f32router", lens, d, E, 64, dtype="f32", seed=45, capacity_factor=1.0)
+    inp = synth.draw(wl)
+    check_route(inp, caps_for(wl, inp), 1.0)
+
+
 def test_long_group_route_only():
     # a column longer than the LDS-cached top-k path
     wl = synth.small("long", [20000, 777], 64, 4, 64, seed=18, capacity_factor=1.5)
