@@ -199,69 +199,136 @@ __global__ __launch_bounds__(64 * TG * RouterCfg<ET>::KS) void router_softmax_bf
   }
 }
 
-// fp32 storage: plain fp32 FMA, fp32 sums of 32-wide K chunks added in K order.
-constexpr int RF_ROWS = 32;
-constexpr int RF_KC = 32;
-
+// fp32 storage: plain fp32 FMA, two-level sums: each 32-wide K chunk of a logit in its
+// own running sum, the chunk sums added in K order (rounding error grows with the chunk
+// and chunk counts, not d).  TR tokens per workgroup; KC wide K tiles of X and Wg go
+// through LDS, the next tile's loads in flight behind the sums of this one.  The chunk
+// sums of a tile are shared out over all threads (a thread: one token, one chunk, four
+// experts) and then added in K order by the thread that owns the logit, so that a
+// few tokens and experts still fill a workgroup: latency bounds these sizes (2048
+// tokens x 16 experts, d 1024: 88 us with one thread per logit and 32 tokens per
+// workgroup).
+template <int KC, int TR>
 __global__ __launch_bounds__(256) void router_softmax_f32_kernel(
     const float* __restrict__ X, const float* __restrict__ Wg, float* __restrict__ S,
     float* __restrict__ ST, int N, int d, int E, float inv_tau) {
-  __shared__ float sX[RF_ROWS][RF_KC + 1];
-  __shared__ float sW[256][RF_KC + 1];
-  __shared__ float sZ[RF_ROWS][257];
+  constexpr int KS = KC / 32, LD = KC + 4;
+  constexpr int ME = KC == 256 ? 32 : (KC == 64 ? 128 : 256);   // most experts
+  constexpr int QW = ME * KC / 4 / 256, QX = TR * KC / 4 / 256;   // 16-byte loads per thread
+  constexpr int QO = TR * ME / 256;                               // logits per owner
+  static_assert(TR * KC % 1024 == 0 || TR * KC < 1024, "whole loads");
+  constexpr int QX1 = QX > 0 ? QX : 1;
+  __shared__ __attribute__((aligned(16))) float sX[TR * LD];
+  __shared__ __attribute__((aligned(16))) float sW[ME * LD];
+  __shared__ float sP[KS * TR * ME];              // chunk sums; then the logits and scores
   const int tid = threadIdx.x;
-  const int row0 = blockIdx.x * RF_ROWS;
-  const int nout = RF_ROWS * E;
-  float acc[32];
+  const int row0 = blockIdx.x * TR;
+  const int nout = TR * E;
+  const int EQ = (E + 3) >> 2;
+  f32x4 xr[QX1], wr[QW];
+  auto load = [&](int k0) {
 #pragma unroll
-  for (int q = 0; q < 32; ++q) acc[q] = 0.f;
-  for (int kc = 0; kc < d; kc += RF_KC) {
-    for (int c = tid; c < RF_ROWS * RF_KC; c += 256) {
-      const int r = c / RF_KC, k = c % RF_KC;
-      const int row = row0 + r;
-      sX[r][k] = (row < N) ? X[(size_t)row * d + kc + k] : 0.f;
+    for (int q = 0; q < QX1; ++q) {
+      const int c = tid + q * 256, r = c / (KC / 4), k = k0 + c % (KC / 4) * 4;
+      const int row = row0 + r < N ? row0 + r : N - 1;          // clamped: not used past the ends
+      xr[q] = *reinterpret_cast<const f32x4*>(X + (size_t)row * d + (k < d ? k : d - 4));
     }
-    for (int c = tid; c < E * RF_KC; c += 256) {
-      const int e = c / RF_KC, k = c % RF_KC;
-      sW[e][k] = Wg[(size_t)e * d + kc + k];
+#pragma unroll
+    for (int q = 0; q < QW; ++q) {
+      const int c = tid + q * 256, e = c / (KC / 4), k = k0 + c % (KC / 4) * 4;
+      wr[q] = *reinterpret_cast<const f32x4*>(Wg + (size_t)(e < E ? e : E - 1) * d +
+                                              (k < d ? k : d - 4));
+    }
+  };
+  float acc[QO];
+#pragma unroll
+  for (int q = 0; q < QO; ++q) acc[q] = 0.f;
+  load(0);
+  for (int k0 = 0; k0 < d; k0 += KC) {
+#pragma unroll
+    for (int q = 0; q < QX1; ++q) {
+      const int c = tid + q * 256, r = c / (KC / 4);
+      if (r < TR) *reinterpret_cast<f32x4*>(&sX[r * LD + c % (KC / 4) * 4]) = xr[q];
+    }
+#pragma unroll
+    for (int q = 0; q < QW; ++q) {
+      const int c = tid + q * 256, e = c / (KC / 4);
+      if (e < E) *reinterpret_cast<f32x4*>(&sW[e * LD + c % (KC / 4) * 4]) = wr[q];
     }
     __syncthreads();
+    if (k0 + KC < d) load(k0 + KC);
+    const int ks_n = (d - k0 < KC ? d - k0 : KC) / 32;     // chunks of this tile
+    for (int it = tid; it < ks_n * TR * EQ; it += 256) {
+      const int eq = it % EQ, r = it / EQ % TR, ks = it / (EQ * TR);
+      const int xo = r * LD + ks * 32;
+      int wo[4];
+      float a[4];
 #pragma unroll
-    for (int q = 0; q < 32; ++q) {
-      const int o = tid + q * 256;
-      if (o < nout) {
-        const int r = o / E, e = o % E;
-        // two-level sum: each K chunk in its own partial, the partials added in
-        // K order (rounding error grows with the chunk and chunk counts, not d)
-        float a = 0.f;
-        for (int k = 0; k < RF_KC; ++k) a = fmaf(sX[r][k], sW[e][k], a);
-        acc[q] += a;
+      for (int i = 0; i < 4; ++i) {
+        wo[i] = (eq + i * EQ < E ? eq + i * EQ : E - 1) * LD + ks * 32;
+        a[i] = 0.f;
       }
+#pragma unroll 2
+      for (int k = 0; k < 32; k += 4) {
+        const f32x4 xv = *reinterpret_cast<const f32x4*>(&sX[xo + k]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const f32x4 wv = *reinterpret_cast<const f32x4*>(&sW[wo[i] + k]);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) a[i] = fmaf(xv[u], wv[u], a[i]);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (eq + i * EQ < E) sP[(ks * TR + r) * E + eq + i * EQ] = a[i];
     }
     __syncthreads();
-  }
 #pragma unroll
-  for (int q = 0; q < 32; ++q) {
+    for (int q = 0; q < QO; ++q) {
+      const int o = tid + q * 256;
+      if (o < nout)
+        for (int ks = 0; ks < ks_n; ++ks) acc[q] += sP[ks * nout + o];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < QO; ++q) {
     const int o = tid + q * 256;
-    if (o < nout) sZ[o / E][o % E] = acc[q] * inv_tau;
+    if (o < nout) sP[o] = acc[q] * inv_tau;
   }
   __syncthreads();
   const int lane = tid & 63, wave = tid >> 6;
-  for (int r = wave; r < RF_ROWS; r += 4) {
-    const int row = row0 + r;
-    if (row >= N) break;
+  for (int r = wave; r < TR && row0 + r < N; r += 4) {
+    float* z = sP + r * E;
     float m = -INFINITY;
-    for (int e = lane; e < E; e += 64) m = fmaxf(m, sZ[r][e]);
+    for (int e = lane; e < E; e += 64) m = fmaxf(m, z[e]);
     for (int o = 1; o < 64; o <<= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
     float s = 0.f;
-    for (int e = lane; e < E; e += 64) s += expf(sZ[r][e] - m);
+    for (int e = lane; e < E; e += 64) s += expf(z[e] - m);
     for (int o = 1; o < 64; o <<= 1) s += __shfl_xor(s, o, 64);
     for (int e = lane; e < E; e += 64) {
-      const float p = expf(sZ[r][e] - m) / s;
-      S[(size_t)row * E + e] = p;
-      ST[(size_t)e * N + row] = p;
+      const float p = expf(z[e] - m) / s;
+      S[(size_t)(row0 + r) * E + e] = p;
+      z[e] = p;
     }
   }
+  __syncthreads();
+  for (int c = tid; c < nout; c += 256) {         // ST: TR consecutive tokens of an expert
+    const int e = c / TR, r = c % TR;
+    if (row0 + r < N) ST[(size_t)e * N + row0 + r] = sP[r * E + e];
+  }
+}
+
+template <int KC>
+hipError_t run_router_f32(const float* x, const float* w, float* S, float* ST, int N, int d, int E,
+                          float inv_tau, hipStream_t st) {
+  // 32 tokens per workgroup re-read the router matrix a quarter as often, once the
+  // tokens still fill every CU twice over; 8 fill the CUs from 2048 tokens on
+  if (N >= 2 * 256 * 32)
+    router_softmax_f32_kernel<KC, 32><<<(N + 31) / 32, 256, 0, st>>>(x, w, S, ST, N, d, E, inv_tau);
+  else
+    router_softmax_f32_kernel<KC, 8><<<(N + 7) / 8, 256, 0, st>>>(x, w, S, ST, N, d, E, inv_tau);
+  return hipGetLastError();
 }
 
 
@@ -280,10 +347,11 @@ hipError_t launch_router_softmax(int dtype, const void* X, const void* Wg, float
                                  int N, int d, int E, float inv_tau, hipStream_t st) {
   if (N == 0) return hipSuccess;
   if (dtype == DT_F32) {
-    const int grid = (N + RF_ROWS - 1) / RF_ROWS;
-    router_softmax_f32_kernel<<<grid, 256, 0, st>>>((const float*)X, (const float*)Wg, S, ST, N,
-                                                    d, E, inv_tau);
-    return hipGetLastError();
+    const float* x = (const float*)X;
+    const float* w = (const float*)Wg;
+    if (E <= 32) return run_router_f32<256>(x, w, S, ST, N, d, E, inv_tau, st);
+    if (E <= 128) return run_router_f32<64>(x, w, S, ST, N, d, E, inv_tau, st);
+    return run_router_f32<32>(x, w, S, ST, N, d, E, inv_tau, st);
   }
   const bf16_t* x = (const bf16_t*)X;
   const bf16_t* w = (const bf16_t*)Wg;
