@@ -313,6 +313,14 @@ def test_topk_every_path(lens, ties):
     check_route(inp, caps, 1.0)
 
 
+@pytest.mark.parametrize("lens", [[8192], [8193, 8191], [16384, 1], [16385, 100], [32768, 2049],
+                                  [32769]])
+@pytest.mark.parametrize("ties", [False, True])
+def test_topk_long_columns(lens, ties):
+    # 16 waves per column with 8, 16 and 32 keys per lane, and one token past each
+    test_topk_every_path(lens, ties)
+
+
 def test_ties_zero_router():
     # Wg = 0: every score is exactly 1/E and each expert takes the first k tokens
     wl = synth.small("ties", [64, 40], 64, 8, 64, seed=19, capacity_factor=2.0)
