@@ -198,6 +198,19 @@ def test_expert_buffer_row_counts(k):
     full_case(wl, inp=inp)
 
 
+@pytest.mark.parametrize("k,d,h", [
+    (300, 384, 320),     # last row block of 44 rows; half-full last column blocks
+    (384, 320, 576),     # ... of 128 rows; 64 columns past the last full block
+    (430, 640, 192),     # ... of 174 rows
+    (449, 576, 448),     # ... of 193 rows: a whole block; 64 and 192 columns
+])
+def test_short_last_blocks(k, d, h):
+    wl = synth.small(f"tails{k}", [1024], d, 4, h, seed=46, capacity_factor=k / 256, backward=True)
+    inp = synth.draw(wl, with_dy=True)
+    assert int(np.sum(caps_for(wl, inp))) == k
+    full_case(wl, inp=inp)
+
+
 def test_zero_capacity_everywhere():
     wl = synth.small("k0", [100, 50], 64, 8, 64, seed=14, capacity_factor=0.0, backward=True)
     out = full_case(wl)
