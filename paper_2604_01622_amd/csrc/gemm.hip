@@ -893,13 +893,18 @@ hipError_t run_dma_var(GemmParams p, long max_rows, hipStream_t st) {
 
 // Row blocks of the forward expert products: 192 when they pad the expert
 // buffers enough less than blocks of 256 (one 2048-token sequence at c(t) =
-// 12 - 8t has 373 rows per expert: 384 computed instead of 512), 128 for
-// buffers of at most 128 rows (that sequence at t = 1).  A 192-row tile (96 x 64
-// per wave) does three quarters of a 256-row tile's work in 0.875 of its time,
-// a 128-row tile (64 x 64 per wave) half the work in 0.74 of the time (W1/W3),
-// so a computed row costs 7/6 and 1.47 times as much.  Every choice keeps an
-// expert's row blocks side by side on one XCD, so its weights are fetched once.
+// 12 - 8t has 373 rows per expert: 384 computed instead of 512).  A 192-row tile (96 x 64
+// per wave) does three quarters of a 256-row tile's work in 0.875 of its time, so a
+// computed row costs 7/6 as much.  Every choice keeps an expert's row blocks side by
+// side on one XCD, so its weights are fetched once.
+// Buffers of at most 128 or 64 rows (that sequence at t = 1; a short sequence) are one
+// row block that only streams the weights: what counts is loads in flight, so three
+// stages instead of two, and for 64 rows 64 x 128 tiles, two workgroups a CU.  Measured
+// with 64 experts, d 2048, h 1024 (805 MB of weights; 128-row tiles of two stages
+// before): 32 rows W1/W3 132 -> 110 us (4.9 TB/s) and W2 57 -> 50, 128 rows 142 -> 132
+// and 69 -> 62.  64-wide columns, two or four stages and 32-row tiles are all slower.
 int fwd_block_rows(int M) {
+  if (M <= 64) return 64;
   if (M <= 128) return 128;
   const long r256 = (M + 255) / 256 * 256L, r192 = (M + 191) / 192 * 192L;
   return r192 * 7 < r256 * 6 ? 192 : 256;
@@ -1259,7 +1264,8 @@ hipError_t launch_gemm_w13(int dtype, const void* Xe, const void* W1, const void
     return run_dma<256, 256, 2, 4, 64, 2, true, true, EPI_SWIGLU, false, G_SH_W13>(p, st);
   }
   switch (fwd_block_rows(M)) {
-    case 128: return run_dma<128, 256, 2, 4, 64, 2, true, true, EPI_SWIGLU, false, G_W13>(p, st);
+    case 64: return run_dma<64, 128, 2, 2, 64, 3, true, true, EPI_SWIGLU, false, G_W13>(p, st);
+    case 128: return run_dma<128, 128, 2, 2, 64, 3, true, true, EPI_SWIGLU, false, G_W13>(p, st);
     case 192: return run_dma<192, 256, 2, 4, 64, 2, true, true, EPI_SWIGLU, false, G_W13>(p, st);
     default: return run_dma<256, 256, 2, 4, 64, 2, true, true, EPI_SWIGLU, false, G_W13, OPT_TAILS>(p, st);
   }
@@ -1276,7 +1282,8 @@ hipError_t launch_gemm_w2(int dtype, const void* A, const void* W2, void* O, int
   if (dtype == DT_F32) return run_f32<true, true, EPI_STORE>(p, st);
   if (shared) return run_dma<256, 256, 4, 2, 64, 2, true, true, EPI_STORE, false, G_SH_W2>(p, st);
   switch (fwd_block_rows(M)) {
-    case 128: return run_dma<128, 256, 2, 4, 64, 2, true, true, EPI_STORE, false, G_W2>(p, st);
+    case 64: return run_dma<64, 128, 2, 2, 64, 3, true, true, EPI_STORE, false, G_W2>(p, st);
+    case 128: return run_dma<128, 256, 2, 4, 64, 3, true, true, EPI_STORE, false, G_W2>(p, st);
     case 192: return run_dma<192, 256, 2, 4, 64, 2, true, true, EPI_STORE, false, G_W2>(p, st);
     default: return run_dma<256, 256, 4, 2, 64, 2, true, true, EPI_STORE, false, G_W2, OPT_TAILS>(p, st);
   }

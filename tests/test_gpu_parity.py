@@ -211,6 +211,16 @@ def test_short_last_blocks(k, d, h):
     full_case(wl, inp=inp)
 
 
+@pytest.mark.parametrize("k,d,h", [(1, 64, 64), (33, 320, 192), (64, 192, 320), (65, 448, 64),
+                                   (128, 64, 448)])
+def test_single_row_block_buffers(k, d, h):
+    # one row block of 64 or 128 rows, ragged column blocks, fewer k-steps than stages
+    wl = synth.small(f"one{k}", [512], d, 4, h, seed=47, capacity_factor=k / 128, backward=True)
+    inp = synth.draw(wl, with_dy=True)
+    assert int(np.sum(caps_for(wl, inp))) == k
+    full_case(wl, inp=inp)
+
+
 def test_zero_capacity_everywhere():
     wl = synth.small("k0", [100, 50], 64, 8, 64, seed=14, capacity_factor=0.0, backward=True)
     out = full_case(wl)
