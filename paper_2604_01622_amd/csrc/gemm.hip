@@ -4,23 +4,34 @@
 // a uniform batch of E problems; ragged per-group capacities only change M.
 //
 // bf16: one pipelined kernel (gemm_dma_kernel) for every product of the
-// forward and backward.  v_mfma_f32_32x32x16_bf16 with fp32 accumulation; a
-// 256 x 256 output tile per workgroup of 8 waves (2 per SIMD, 64 x 128 or
-// 128 x 64 each; the forward products take 192- or 128-row tiles, 96 x 64 or
-// 64 x 64 per wave, when those pad short expert buffers less);
-// K advances 64 at a time through a 2-stage LDS ring filled straight from
-// global memory by global_load_lds_dwordx4 (no VGPR staging).  K-contiguous
-// operands sit in LDS as 128-byte rows with XOR-swizzled 16-byte chunks
-// (conflict-free fragment reads); K-major operands (the weight gradients'
-// token-row contractions, and the weights in the dA and dX products) stay
-// K-major in LDS and are read with the transposing ds_read_b64_tr_b16.  The MFMAs of each k-step alternate with the
-// next step's fragment reads and, once the barrier has freed a stage, with its
-// refill's DMA (for K-contiguous products half of it then, half in the next
-// step's first sub-step), so LDS latency hides behind MFMAs in flight.  The
-// MFMAs take the B fragment first, so each lane ends with four consecutive
-// output columns of a row, staged through LDS with 16-byte writes for
-// coalesced stores.  Tiles are numbered so that consecutive ones share an
-// expert and stay on one XCD.
+// forward and backward.  v_mfma_f32_16x16x32_bf16 with fp32 accumulation; a
+// 256 x 256 output tile per workgroup (the forward products take 192-, 128- or 64-row
+// tiles when those pad short expert buffers less).  K advances 64 at a time through a
+// 2-stage LDS ring filled straight from global memory by buffer_load_dwordx4 ... lds
+// (no VGPR staging, one offset register per load).  K-contiguous operands sit in LDS as
+// 128-byte rows with XOR-swizzled 16-byte chunks (conflict-free fragment reads);
+// K-major operands (the weight gradients' token-row contractions, and the weights in
+// the dA and dX products) stay K-major in LDS and are read with the transposing
+// ds_read_b64_tr_b16.  The MFMAs alternate with the next sub-step's fragment reads
+// and, once the barrier has freed a stage, with its refill's DMA (half of it then,
+// half in the next step), so LDS latency hides behind MFMAs in flight.  The MFMAs
+// take the B fragment first, so each lane ends with four consecutive output columns
+// of a row, staged through LDS with 16-byte writes for coalesced stores.  Tiles are
+// numbered so that consecutive ones share an expert and stay on one XCD.
+//
+// What bounds it: at 8 x 2048 tokens the chip's power limit and the LDS port, which a
+// k-step keeps busy about as long as the matrix cores (64 KiB written, 128 KiB read by
+// four waves of 128 x 128 or 192 KiB by eight of 64 x 128).  Hence 16x16x32 MFMAs, which
+// move half the accumulator bytes per product of 32x32x16 ones and so let the clock
+// rise, buffer loads (with global_load_lds the compiler waits for every LDS read in
+// flight, lgkmcnt(0), before each use; with buffer loads it counts), and four waves
+// where both operands are K-contiguous.  K-major operands keep eight: their fragments
+// take twice the reads, and one wave per SIMD leaves those exposed (dW1/dW3 of one
+// 2048-token sequence 204 us against 235).  Measured on one card, 64 experts x 2071
+// rows, d 2048, h 1024, against 32x32x16 MFMAs, eight waves and global loads: W1/W3 1053
+// -> 1015 us, W2 532 -> 542, dA 642 -> 630, dW2 512 -> 461, dXe 1015 -> 983, dW1/dW3 1043
+// -> 899 within a step that as a whole goes 5127 -> 4853 (the kernels share one power
+// budget); one 2048-token sequence 916 -> 871 us.
 //
 // The products that read the selected tokens' rows (of X, or of the output
 // gradient dY) gather them in the operand load: the W1/W3 and dA products per
@@ -128,6 +139,28 @@ __device__ __forceinline__ void dma16(const void* g, void* lds) {
 #endif
 }
 
+// The same from a buffer resource: a uniform base, a 32-bit byte offset per lane and a
+// uniform one, so a K-contiguous operand's loads need one register each and no vector
+// arithmetic per step.
+#if defined(__HIP_DEVICE_COMPILE__)
+using Rsrc = __amdgpu_buffer_rsrc_t;
+__device__ __forceinline__ Rsrc make_rsrc(const void* base, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
+}
+__device__ __forceinline__ void dma16_buf(Rsrc r, uint32_t voff, int soff, void* lds) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 16,
+                                           (int)voff, soff, 0, 0);
+}
+#else
+using Rsrc = int;
+__device__ inline Rsrc make_rsrc(const void*, uint32_t) { return 0; }
+__device__ inline void dma16_buf(Rsrc, uint32_t, int, void*) {}
+#endif
+
+// sizes of buffers that are never read past their end (at most 2^32 - 128 bytes, the
+// library's limit), and an offset past any of them
+constexpr uint32_t BUF_ALL = 0xffffff80u, BUF_PAST = 0xfffffff0u;
+
 constexpr int vmcnt_imm(int n) { return (n & 15) | (((n >> 4) & 3) << 14) | (7 << 4) | (15 << 8); }
 
 // Each operand is K-contiguous (stored [rows][K]) or K-major (stored
@@ -136,8 +169,7 @@ constexpr int vmcnt_imm(int n) { return (n & 15) | (((n >> 4) & 3) << 14) | (7 <
 // XOR-swizzled by k) and read with the transposing ds_read_b64_tr_b16: in each 16-lane group, lane j addresses the
 // 4 consecutive columns 4*(j%4).. of row kbase + j/4, and lane i receives
 // column i of rows kbase..kbase+3 -- two such reads make one MFMA fragment.
-// Rows past the valid K (ragged tail) and columns past the operand's width are
-// fetched from a zero block, so the MFMAs see exact zeros there.
+// Rows past the valid K (ragged tail) read as exact zeros.
 
 typedef short v4i16 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) v4i16 lds_v4i16;
@@ -161,14 +193,12 @@ struct DmaOperand {
   static_assert(KC || (R % 128 == 0), "K-major tiles are multiples of 128 wide");
 };
 
-// Chunk swizzles, chosen by measuring the fragment-read pattern on gfx950:
-// K-contiguous rows of 64 or 128 bytes, and K-major rows (by k).
-template <int KSTEP>
-__device__ __forceinline__ int kc_swz(int row) {
-  if constexpr (KSTEP == 64) return (row ^ (row >> 3)) & 7;
-  else return ((row >> 1) ^ (row >> 2)) & 3;
-}
-__device__ __forceinline__ int km_swz(int k) { return (k & 3) << 2; }
+// Chunk swizzles, for the fragment-read patterns (SQ_LDS_BANK_CONFLICT reads zero in the
+// main loops): 128-byte K-contiguous rows, whose 16 (fp32: 32) rows of a fragment read two
+// to a 256-byte bank line, and K-major rows (by k), whose four 16-lane groups read 32
+// bytes of four rows each.
+__device__ __forceinline__ int kc_swz(int row) { return (row >> 1) & 7; }
+__device__ __forceinline__ int km_swz(int k) { return ((k & 3) << 2) | ((k >> 2) & 2); }
 
 // Options of an instantiation (bf16; see GemmParams): OPT_GA / OPT_GB gather
 // the rows of a K-major A / B through p.ka_rows / p.kb_rows.  OPT_TAILS:
@@ -180,9 +210,9 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmParams& p, const TileCoo
                                               char* smem) {
   constexpr int NT = 64 * WGM * WGN;
   constexpr int WM = BM / WGM, WN = BN / WGN;
-  constexpr int MB = WM / 32, NB = WN / 32;
-  constexpr int KK = KSTEP / 16;
-  static_assert(KSTEP == 32 || KSTEP == 64, "K step");
+  constexpr int MB = WM / 16, NB = WN / 16, MH = MB / 2, NH = NB / 2;
+  constexpr int KK = KSTEP / 32;
+  static_assert(KSTEP == 64 && MB % 2 == 0 && NB % 2 == 0, "two 32-wide sub-steps, whole halves");
   static_assert(STAGES >= 2 && STAGES <= 5, "ring depth");
   using OA = DmaOperand<BM, A_KC, NT, KSTEP>;
   using OB = DmaOperand<BN, B_KC, NT, KSTEP>;
@@ -216,12 +246,12 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmParams& p, const TileCoo
 
   // ---- DMA sources.  Load q of a thread fills 1 KiB block (wave*L + q) of
   // the operand's stage area: 64 chunks, lane -> chunk.
-  // K-contiguous: the row pointer of the chunk, offset by kt * KSTEP per step.
-  // K-major: the chunk's address at k-step 0 (or the zero block for columns
-  // past the operand), advanced by KSTEP rows after every issue; rows past the
-  // valid K read the zero block instead.  K-major gathered (OPT_GA / OPT_GB):
-  // the chunk's column in row 0 of the operand (clamped into the row: columns
-  // past the width produce outputs that are not stored); the source rows of
+  // Every load has one byte offset from its operand's uniform base (an operand is
+  // below 2^32 bytes), the step's offset being uniform.  K-contiguous: the chunk in its
+  // row (clamped: rows past the end produce outputs that are not stored).
+  // K-major: the chunk at k-step 0, its column clamped into the operand likewise; rows
+  // past the valid K ask for an offset past the buffer, which reads as zero.
+  // K-major gathered (OPT_GA / OPT_GB): the chunk's column; the source rows of
   // the next k-step's 64 rows are held one per lane (fetched one step ahead,
   // the first two at set-up so that the prologue waits for no index) and each
   // load takes its row's with a lane read.  Rows past the valid K re-read a
@@ -232,14 +262,8 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmParams& p, const TileCoo
   static_assert((!GA || OA::CPR == 32) && (!GB || OB::CPR == 32),
                 "a gathered load covers two k rows of 256 columns");
   static_assert(!(GA || GB) || KSTEP == 64, "one source row per lane and k-step");
-  const bf16_t* a_src[OA::LOADS];
-  int a_row[OA::LOADS];
-  long a_step[OA::LOADS];
-  const bf16_t* b_src[OB::LOADS];
-  int b_row[OB::LOADS];
-  long b_step[OB::LOADS];
-  // source row of row k (< K) of a gathered operand; rows past kv re-read the
-  // last valid one (their loads take the zero block)
+  uint32_t a_off[OA::LOADS], b_off[OB::LOADS];
+  // source row of row k (< K) of a gathered operand; rows past kv re-read the last
   auto k_row = [&](const int32_t* rows, int k, int kv) -> int {
     return rows[(size_t)e * p.k_rows_bs + (k < kv ? k : kv - 1)];
   };
@@ -266,60 +290,46 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmParams& p, const TileCoo
   for (int q = 0; q < OA::LOADS; ++q) {
     const int id = (wave * OA::LOADS + q) * 64 + lane;
     if constexpr (A_KC) {
-      const int row = id / OA::CPR, lc = (id % OA::CPR) ^ kc_swz<KSTEP>(row);
+      const int row = id / OA::CPR, lc = (id % OA::CPR) ^ kc_swz(row);
       int r = m0 + row;
       r = r < M ? r : M - 1;
       if (p.a_rows) {
         const int tok = p.a_rows[(size_t)e * p.a_rows_bs + tc.row0 + r];
-        a_src[q] = reinterpret_cast<const bf16_t*>(p.A) + (size_t)tok * p.lda + lc * 8;
+        a_off[q] = ((uint32_t)tok * (uint32_t)p.lda + lc * 8) * 2;
       } else {
-        a_src[q] = Ab + (size_t)r * p.lda + lc * 8;
+        a_off[q] = ((uint32_t)r * (uint32_t)p.lda + lc * 8) * 2;
       }
     } else {
       const int row = id / OA::CPR, lc = (id % OA::CPR) ^ km_swz(row);
-      const int col = m0 + lc * 8;   // first column of the chunk
-      a_row[q] = row;                // k within the step
-      if constexpr (GA) {
-        a_src[q] = reinterpret_cast<const bf16_t*>(p.A) + (col < M ? col : M - 8);
-      } else {
-        a_src[q] = col < M ? Ab + (size_t)row * p.lda + col : g_zero_block;
-        a_step[q] = col < M ? (long)KSTEP * p.lda : 0;
-      }
+      const int col = m0 + lc * 8 < M ? m0 + lc * 8 : (M - 1) & ~7;   // first column of the chunk
+      a_off[q] = ((GA ? 0u : (uint32_t)row * (uint32_t)p.lda) + col) * 2;
     }
   }
 #pragma unroll
   for (int q = 0; q < OB::LOADS; ++q) {
     const int id = (wave * OB::LOADS + q) * 64 + lane;
     if constexpr (B_KC) {
-      const int row = id / OB::CPR, lc = (id % OB::CPR) ^ kc_swz<KSTEP>(row);
-      const bf16_t* rp;
-      if constexpr (EPI == EPI_SWIGLU) {
-        int r = n0 + row % (BN / 2);
-        r = r < p.N ? r : p.N - 1;
-        rp = (row < BN / 2 ? Bb : B2b) + (size_t)r * p.ldb;
-      } else {
-        int r = n0 + row;
-        r = r < p.N ? r : p.N - 1;
-        rp = Bb + (size_t)r * p.ldb;
-      }
-      b_src[q] = rp + lc * 8;
+      const int row = id / OB::CPR, lc = (id % OB::CPR) ^ kc_swz(row);
+      int r = n0 + (EPI == EPI_SWIGLU ? row % (BN / 2) : row);
+      r = r < p.N ? r : p.N - 1;
+      b_off[q] = ((uint32_t)r * (uint32_t)p.ldb + lc * 8) * 2;
     } else {
       const int row = id / OB::CPR, lc = (id % OB::CPR) ^ km_swz(row);
-      const int col = n0 + lc * 8;
-      b_row[q] = row;
-      if constexpr (GB) {
-        b_src[q] = reinterpret_cast<const bf16_t*>(p.B) + (col < p.N ? col : p.N - 8);
-      } else {
-        b_src[q] = col < p.N ? Bb + (size_t)row * p.ldb + col : g_zero_block;
-        b_step[q] = col < p.N ? (long)KSTEP * p.ldb : 0;
-      }
+      const int col = n0 + lc * 8 < p.N ? n0 + lc * 8 : (p.N - 1) & ~7;
+      b_off[q] = ((GB ? 0u : (uint32_t)row * (uint32_t)p.ldb) + col) * 2;
     }
   }
-  // K-major B split at k_split: from row k_split of B to row 0 of B2
-  const long b_jump =
-      (!B_KC && B2b) ? (long)(((intptr_t)B2b - (intptr_t)(Bb + (size_t)p.k_split * p.ldb)) /
-                              (intptr_t)sizeof(bf16_t))
-                     : 0;
+  // a SwiGLU wave's rows all lie in W1 or all in W3
+  static_assert(EPI != EPI_SWIGLU || (BN / 2) % (OB::LOADS * 8) == 0, "one weight per wave");
+  const Rsrc a_rsrc =
+      make_rsrc((A_KC ? p.a_rows != nullptr : GA) ? p.A : (const void*)Ab,
+                A_KC || GA ? BUF_ALL : (uint32_t)p.kv_a * (uint32_t)p.lda * 2u);
+  const Rsrc b_rsrc =
+      make_rsrc(EPI == EPI_SWIGLU && wave * OB::LOADS * 8 >= BN / 2 ? B2b : Bb,
+                B_KC || GB ? BUF_ALL
+                           : (uint32_t)(p.kv_b < p.k_split ? p.kv_b : p.k_split) * (uint32_t)p.ldb * 2u);
+  // K-major B split at k_split (a multiple of the k-step): steps from there on read B2
+  const Rsrc b2_rsrc = make_rsrc(!B_KC && B2b ? B2b : Bb, BUF_ALL);
   // Issues k-step kt; the calls come with kt = 0, 1, 2, ... in order.
   // Loads [lo, hi) of k-step kt (A's loads first, then B's); each load of a
   // k-step is issued exactly once and the k-steps in order.
@@ -330,39 +340,43 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmParams& p, const TileCoo
     constexpr bool FULL = decltype(full_step)::value;
     constexpr bool FIRST = decltype(first)::value;
     char* base = smem + stage * STAGE_BYTES;
+    // the loads of a K-major operand: rows past the valid K ask for an offset past the
+    // buffer, which reads as zero
+    auto km_load = [&](Rsrc r, uint32_t off, int row, int k0, int kv, uint32_t ld, void* lds) {
+      const uint32_t step = (uint32_t)k0 * ld * 2u;
+      if constexpr (FULL) dma16_buf(r, off, (int)step, lds);
+      else dma16_buf(r, k0 + row < kv ? off + step : BUF_PAST, 0, lds);
+    };
 #pragma unroll
     for (int q = 0; q < OA::LOADS; ++q) {
       if (q < lo || q >= hi) continue;
-      const bf16_t* g;
-      if constexpr (A_KC) {
-        g = a_src[q] + kt * KSTEP;
-      } else if constexpr (GA) {
-        g = a_src[q] + (size_t)pick_row(a_kidx, wave * OA::LOADS + q) * p.lda;
-      } else {
-        g = (FULL || kt * KSTEP + a_row[q] < p.kv_a) ? a_src[q] : g_zero_block;
-        a_src[q] += a_step[q];
-      }
-      dma16(g, base + (wave * OA::LOADS + q) * 1024);
+      char* lds = base + (wave * OA::LOADS + q) * 1024;
+      if constexpr (A_KC)
+        dma16_buf(a_rsrc, a_off[q], kt * KSTEP * 2, lds);
+      else if constexpr (GA)
+        dma16_buf(a_rsrc, a_off[q] + (uint32_t)pick_row(a_kidx, wave * OA::LOADS + q) * (uint32_t)p.lda * 2u, 0, lds);
+      else
+        km_load(a_rsrc, a_off[q], ((wave * OA::LOADS + q) * 64 + lane) / OA::CPR, kt * KSTEP, p.kv_a, p.lda, lds);
     }
     if constexpr (GA) {   // every A load of step kt has gone out: rows of step kt + 1
-      if (hi >= OA::LOADS)
+      if (lo < OA::LOADS && hi >= OA::LOADS)
         a_kidx = FIRST ? a_kidx1 : k_row(p.ka_rows, (kt + 1) * KSTEP + lane, p.kv_a);
     }
 #pragma unroll
     for (int q = 0; q < OB::LOADS; ++q) {
       if (OA::LOADS + q < lo || OA::LOADS + q >= hi) continue;
-      const bf16_t* g;
+      char* lds = base + OA::BYTES + (wave * OB::LOADS + q) * 1024;
       if constexpr (B_KC) {
-        g = b_src[q] + kt * KSTEP;
+        dma16_buf(b_rsrc, b_off[q], kt * KSTEP * 2, lds);
       } else if constexpr (GB) {
-        g = b_src[q] + (size_t)pick_row(b_kidx, wave * OB::LOADS + q) * p.ldb;
+        dma16_buf(b_rsrc, b_off[q] + (uint32_t)pick_row(b_kidx, wave * OB::LOADS + q) * (uint32_t)p.ldb * 2u, 0, lds);
       } else {
-        g = (FULL || kt * KSTEP + b_row[q] < p.kv_b) ? b_src[q] : g_zero_block;
-        // the next step's row; at k_split it continues in row 0 of B2
-        const bool jump = (kt + 1) * KSTEP == p.k_split && b_step[q] != 0;
-        b_src[q] += b_step[q] + (jump ? b_jump : 0);
+        const int row = ((wave * OB::LOADS + q) * 64 + lane) / OB::CPR;
+        if (kt * KSTEP < p.k_split)
+          km_load(b_rsrc, b_off[q], row, kt * KSTEP, p.kv_b, p.ldb, lds);
+        else
+          km_load(b2_rsrc, b_off[q], row, kt * KSTEP - p.k_split, p.kv_b - p.k_split, p.ldb, lds);
       }
-      dma16(g, base + OA::BYTES + (wave * OB::LOADS + q) * 1024);
     }
     if constexpr (GB) {
       if (hi >= OA::LOADS + OB::LOADS)
@@ -376,72 +390,64 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmParams& p, const TileCoo
   auto b_lds_col = [&](int ni) -> int {
     if constexpr (EPI == EPI_SWIGLU) {
       constexpr int HWN = BN / 2 / WGN;
-      return (ni < NB / 2) ? wn * HWN + ni * 32 : BN / 2 + wn * HWN + (ni - NB / 2) * 32;
+      return (ni < NH) ? wn * HWN + ni * 16 : BN / 2 + wn * HWN + (ni - NH) * 16;
     } else {
-      return wn * WN + ni * 32;
+      return wn * WN + ni * 16;
     }
   };
-  // Fragment addressing.  K-contiguous: lane l reads row base + l % 32 of the
-  // tile, base a multiple of 32 (uniform over the wave), so the row's chunk
-  // swizzle is one per-lane value combined with a uniform one.  K-major: lane l
-  // reads 4 columns from column base + lp of k rows km_k and km_k + 4 (of each
-  // 16-wide step); with base a multiple of 32 the swizzled chunk is base / 8
-  // XOR a per-lane value.  Nothing per fragment is held in registers.
-  const int g16 = lane >> 4, j16 = lane & 15;
-  const int l31 = lane & 31;
-  const int swz_lane = (l31 & 7) ^ (l31 >> 3);
-  auto kc_sw = [&](int base) -> int {
-    if constexpr (KSTEP == 64) return swz_lane ^ ((base >> 3) & 7);
-    else return kc_swz<KSTEP>(base + l31);
-  };
-  const int km_k = 8 * (g16 >> 1) + (j16 >> 2);   // k row (within a 16-step) of a K-major read
-  const int km_lp = 16 * (g16 & 1) + 4 * (j16 & 3);
+  // Fragment addressing (16 rows or columns x 32 k).  K-contiguous: lane l reads row
+  // base + l % 16 of the tile, base a multiple of 16 (uniform over the wave), so the
+  // row's chunk swizzle is a per-lane value.  K-major:
+  // lane l reads 4 columns from column base + lp of k rows km_k and km_k + 4 (of each
+  // 32-wide sub-step); the swizzled chunk is base / 8 XOR a per-lane value.  Nothing
+  // per fragment is held in registers.
+  const int g16 = lane >> 4, l15 = lane & 15;
+  const int km_k = 8 * g16 + (l15 >> 2);            // k row (within a sub-step) of a K-major read
+  const int km_lp = 4 * (l15 & 3);
   const int km_inner = (km_lp & 7) * 2;             // byte offset inside the chunk
   const int km_u = (km_lp >> 3) | km_swz(km_k);     // chunk bits from the lane and the k swizzle
 
-  bf16x8 af[2][MB], bfr[2][NB];
+  bf16x8 af[MB], bfr[NB];
+  auto kc_frag = [&](const char* tile, int base, int kk) -> bf16x8 {
+    const int lc = kk * 4 + g16;
+    return __builtin_bit_cast(
+        bf16x8, *reinterpret_cast<const u32x4*>(tile + (base + l15) * (KSTEP * 2) +
+                                                ((lc ^ (l15 >> 1)) << 4)));
+  };
   auto km_frag = [&](const char* tile, int rowbytes, int base, int kk) -> bf16x8 {
-    const char* p0 = tile + (kk * 16 + km_k) * rowbytes + (((base >> 3) ^ km_u) << 4) + km_inner;
+    const char* p0 = tile + (kk * 32 + km_k) * rowbytes + (((base >> 3) ^ km_u) << 4) + km_inner;
     const v4i16 lo = ds_read_tr16(p0);
     const v4i16 hi = ds_read_tr16(p0 + 4 * rowbytes);
     const v4i16 both[2] = {lo, hi};
     return __builtin_bit_cast(bf16x8, both);
   };
-  auto load_frags = [&](int buf, int stage, int kk) {
+  // half of the A (B) fragments of sub-step kk
+  auto load_a = [&](int stage, int kk, int half) {
     const char* sa = smem + stage * STAGE_BYTES;
-    const char* sbb = sa + OA::BYTES;
-    const int lc = kk * 2 + (lane >> 5);
 #pragma unroll
-    for (int mi = 0; mi < MB; ++mi) {
-      if constexpr (A_KC) {
-        const int base = wm * WM + mi * 32;
-        af[buf][mi] = __builtin_bit_cast(
-            bf16x8, *reinterpret_cast<const u32x4*>(sa + (base + l31) * (KSTEP * 2) +
-                                                    ((lc ^ kc_sw(base)) << 4)));
-      } else
-        af[buf][mi] = km_frag(sa, BM * 2, wm * WM + mi * 32, kk);
+    for (int i = 0; i < MH; ++i) {
+      const int mi = half * MH + i;
+      if constexpr (A_KC) af[mi] = kc_frag(sa, wm * WM + mi * 16, kk);
+      else af[mi] = km_frag(sa, BM * 2, wm * WM + mi * 16, kk);
     }
+  };
+  auto load_b = [&](int stage, int kk, int half) {
+    const char* sb = smem + stage * STAGE_BYTES + OA::BYTES;
 #pragma unroll
-    for (int ni = 0; ni < NB; ++ni) {
-      if constexpr (B_KC) {
-        const int base = b_lds_col(ni);
-        bfr[buf][ni] = __builtin_bit_cast(
-            bf16x8, *reinterpret_cast<const u32x4*>(sbb + (base + l31) * (KSTEP * 2) +
-                                                    ((lc ^ kc_sw(base)) << 4)));
-      } else {
-        bfr[buf][ni] = km_frag(sbb, BN * 2, b_lds_col(ni), kk);
-      }
+    for (int i = 0; i < NH; ++i) {
+      const int ni = half * NH + i;
+      if constexpr (B_KC) bfr[ni] = kc_frag(sb, b_lds_col(ni), kk);
+      else bfr[ni] = km_frag(sb, BN * 2, b_lds_col(ni), kk);
     }
   };
 
-  f32x16 acc[MB][NB];
+  f32x4 acc[MB][NB];
 #pragma unroll
   for (int mi = 0; mi < MB; ++mi)
 #pragma unroll
-    for (int ni = 0; ni < NB; ++ni)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[mi][ni][r] = 0.f;
+    for (int ni = 0; ni < NB; ++ni) acc[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+  constexpr bool EARLY = A_KC && B_KC;   // read order, see below
   // Ring: steps 0..STAGES-1 are issued up front; the end of step kt refills
   // stage kt % STAGES with step kt + STAGES once every wave has read it.  When
   // waiting for step j, the steps issued after it number min(STAGES-1, KT-1-j)
@@ -462,95 +468,100 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmParams& p, const TileCoo
   if (KT > 0) {
     wait_younger(KT - 1 < STAGES - 1 ? KT - 1 : STAGES - 1);
     __builtin_amdgcn_s_barrier();
-    load_frags(0, 0, 0);
+    load_a(0, 0, 0);
+    load_b(0, 0, 0);
+    if constexpr (EARLY) load_b(0, 0, 1);
   }
-  constexpr int NMF = MB * NB;
-  auto mfma_range = [&](int cur, int lo, int hi) {
+  // a quadrant: half of the A blocks times half of the B blocks.  B fragment first: the
+  // 16 x 16 block comes out transposed, each lane holding four consecutive output
+  // columns of one row (16-byte staging writes in the epilogue)
+  constexpr int NMQ = MH * NH;
+  auto quad = [&](int ha, int hb) {
 #pragma unroll
-    for (int q = 0; q < NMF; ++q) {
-      if (q < lo || q >= hi) continue;
-      const int mi = q / NB, ni = q % NB;
-      // B fragment first: the 32 x 32 block comes out transposed, each lane
-      // holding four consecutive output columns of one row (16-byte staging
-      // writes in the epilogue)
-      acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[cur][ni], af[cur][mi],
-                                                              acc[mi][ni], 0, 0, 0);
-    }
+    for (int j = 0; j < NH; ++j)
+#pragma unroll
+      for (int i = 0; i < MH; ++i) {
+        const int mi = ha * MH + i, ni = hb * NH + j;
+        acc[mi][ni] =
+            __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[ni], af[mi], acc[mi][ni], 0, 0, 0);
+      }
   };
 
-
-  // Fragment-read instructions per 16-wide k step (a K-major fragment takes
-  // two).  Inside a stage the MFMAs on the current fragments alternate with
-  // the reads of the next ones (one MFMA, one read, ...).  At a stage end: half
-  // the MFMAs, then this wave's waits and the barrier, then the other half
-  // alternating with the refill's DMA and the next stage's first reads.  Steps
-  // with and without a refill (or a refill's second half) run in separate
-  // straight-line segments, so that no branch splits an interleaved group.
-  constexpr int NRD = MB * (A_KC ? 1 : 2) + NB * (B_KC ? 1 : 2);
-  constexpr int HALF = NMF / 2;
+  // A 32-wide sub-step runs as four quadrants, A0 Bx, A0 By, A1 By, A1 Bx (x alternating
+  // between sub-steps), so that half operands die one by one and one set of fragment
+  // registers is enough.  A1 is read during the first quadrant, the next sub-step's A0
+  // during the third.  EARLY (both operands K-contiguous): its By and Bx are read during
+  // the third and fourth, each fragment after the last MFMA of the one it replaces, a
+  // whole quadrant before their use; K-major operands' twice as many reads are
+  // spread instead, By over the fourth and Bx over the next first (reading them early
+  // costs dW2 12% and dA 6%).  In a stage's last sub-step the waits and the barrier
+  // stand between the second and third quadrants (the stage's last reads are then done),
+  // and the refill's DMA follows in the other two.  Steps with and without a refill (or
+  // a refill's second half) run in separate straight-line segments, so that no branch
+  // splits an interleaved group.
+  constexpr int RA = MH * (A_KC ? 1 : 2), RB = NH * (B_KC ? 1 : 2);   // read instructions
   // A stage's refill is issued in two parts: DMA_HEAD loads after the barrier
   // that frees the stage, the rest in the next step's first sub-step (two
   // stages only: the wait at every step end is then for all outstanding loads).
-  constexpr bool SPLIT_DMA = STAGES == 2 && KK > 1;
-  // (measured: half after the barrier and half in one sub-step beats a quarter
-  // then three sub-steps, none after the barrier, or two tail sub-steps)
-  constexpr int DMA_HEAD = SPLIT_DMA ? LOADS / 2 : LOADS;
-  constexpr int TAIL_SUBS = 1;
-  constexpr int TAIL_PER = (LOADS - DMA_HEAD + TAIL_SUBS - 1) / TAIL_SUBS;
+  constexpr bool SPLIT_DMA = STAGES == 2;
+  constexpr int DMA_HEAD = SPLIT_DMA ? LOADS / 2 : LOADS, DMA_Q3 = DMA_HEAD / 2;
+  // orders a quadrant: after each MFMA its share of the LDS reads and DMA loads
+  auto order = [&](auto reads, auto dmas) {
+    constexpr int RD = decltype(reads)::value, DM = decltype(dmas)::value;
+#pragma unroll
+    for (int q = 0; q < NMQ; ++q) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                     // MFMA
+      if constexpr (DM > 0) __builtin_amdgcn_sched_group_barrier(0x010, (DM + NMQ - 1) / NMQ, 0);   // DMA
+      if constexpr (RD > 0) __builtin_amdgcn_sched_group_barrier(0x100, (RD + NMQ - 1) / NMQ, 0);   // LDS read
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
   auto kstep = [&](int kt, auto refill, auto tail_part, auto full_refill) {
     constexpr bool RF = decltype(refill)::value;
     constexpr bool TAIL = SPLIT_DMA && decltype(tail_part)::value;
     const int stage = kt % STAGES;
-    // TAIL: the second part of the previous step's refill goes out in this
-    // step's first 16-wide sub-step (it still has a whole step to land)
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
-      const int cur = kk & 1;
-      if (kk < TAIL_SUBS && TAIL) {
-        mfma_range(cur, 0, NMF);
-        {
-          const int q0 = DMA_HEAD + kk * TAIL_PER;
-          const int q1 = q0 + TAIL_PER < LOADS ? q0 + TAIL_PER : LOADS;
-          issue_part(kt - 1 + STAGES, (kt - 1) % STAGES, q0, q1, full_refill,
+      const int x = kk & 1;
+      const bool last = kk == KK - 1;
+      using RB_ = std::integral_constant<int, RB>;
+      using NONE_ = std::integral_constant<int, 0>;
+      const int nstage = last ? (kt + 1) % STAGES : stage, nkk = last ? 0 : kk + 1;
+      quad(0, x);
+      if constexpr (!EARLY) load_b(stage, kk, x ^ 1);
+      load_a(stage, kk, 1);
+      order(std::integral_constant<int, EARLY ? RA : RA + RB>{}, NONE_{});
+      quad(0, x ^ 1);
+      if (!last) {
+        // TAIL: the second part of the previous step's refill
+        if constexpr (TAIL) {
+          issue_part(kt - 1 + STAGES, (kt - 1) % STAGES, DMA_HEAD, LOADS, full_refill,
                      std::false_type{});
+          order(NONE_{}, std::integral_constant<int, LOADS - DMA_HEAD>{});
+        } else {
+          __builtin_amdgcn_sched_barrier(0);
         }
-        load_frags(cur ^ 1, stage, kk + 1);
-#pragma unroll
-        for (int q = 0; q < NMF; ++q) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                 // MFMA
-          __builtin_amdgcn_sched_group_barrier(0x010, (TAIL_PER + NMF - 1) / NMF, 0);         // DMA
-          __builtin_amdgcn_sched_group_barrier(0x100, (NRD + NMF - 1) / NMF, 0);             // LDS read
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      } else if (kk + 1 < KK) {
-        mfma_range(cur, 0, NMF);
-        load_frags(cur ^ 1, stage, kk + 1);
-#pragma unroll
-        for (int q = 0; q < NRD; ++q) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // MFMA
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // LDS read
-        }
-        __builtin_amdgcn_sched_group_barrier(0x008, NMF > NRD ? NMF - NRD : 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
       } else {
-        mfma_range(cur, 0, HALF);
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): this wave's reads are done
         if (kt + 1 < KT) wait_younger(KT - 2 - kt < STAGES - 2 ? KT - 2 - kt : STAGES - 2);
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
-        mfma_range(cur, HALF, NMF);
-        if constexpr (RF) issue_part(kt + STAGES, stage, 0, DMA_HEAD, full_refill, std::false_type{});
-        // after the final step this reads a stale stage, harmlessly
-        load_frags(cur ^ 1, (kt + 1) % STAGES, 0);
-#pragma unroll
-        for (int q = 0; q < HALF; ++q) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                           // MFMA
-          if constexpr (RF) __builtin_amdgcn_sched_group_barrier(0x010, (DMA_HEAD + HALF - 1) / HALF, 0);  // DMA
-          __builtin_amdgcn_sched_group_barrier(0x100, (NRD + HALF - 1) / HALF, 0);     // LDS read
-        }
-        __builtin_amdgcn_sched_barrier(0);
       }
+      // after the final step these read a stale stage, harmlessly
+      quad(1, x ^ 1);
+      if constexpr (RF)
+        if (last) issue_part(kt + STAGES, stage, 0, DMA_Q3, full_refill, std::false_type{});
+      load_a(nstage, nkk, 0);
+      if constexpr (EARLY) load_b(nstage, nkk, x ^ 1);
+      if (RF && last) order(std::integral_constant<int, EARLY ? RA + RB : RA>{}, std::integral_constant<int, DMA_Q3>{});
+      else order(std::integral_constant<int, EARLY ? RA + RB : RA>{}, NONE_{});
+      quad(1, x);
+      if constexpr (RF)
+        if (last) issue_part(kt + STAGES, stage, DMA_Q3, DMA_HEAD, full_refill, std::false_type{});
+      load_b(nstage, nkk, EARLY ? x : x ^ 1);
+      if (RF && last) order(RB_{}, std::integral_constant<int, DMA_HEAD - DMA_Q3>{});
+      else order(RB_{}, NONE_{});
     }
   };
   // Straight-line segments, so that no branch splits an interleaved group:
@@ -622,17 +633,16 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmParams& p, const TileCoo
     for (int q = 0; q < NQ; ++q) load_h(0, q);
   }
 #pragma unroll
-  for (int mi = 0; mi < MB; ++mi) {
+  for (int mi = 0; mi < WM / 32; ++mi) {
     const int mbase = m0 + wm * WM + mi * 32;
-    // acc[mi][ni][4 g + i] is row lane % 32 of the slice, column
-    // 32 ni + 8 g + 4 (lane / 32) + i
+    // acc[2 mi + b][ni][i] is row 16 b + lane % 16 of the slice, column
+    // 16 ni + 4 (lane / 16) + i
 #pragma unroll
-    for (int ni = 0; ni < NB; ++ni)
+    for (int b = 0; b < 2; ++b)
 #pragma unroll
-      for (int g = 0; g < 4; ++g)
-        *reinterpret_cast<f32x4*>(&stage_f[(lane & 31) * SLD + ni * 32 + g * 8 + (lane >> 5) * 4]) =
-            f32x4{acc[mi][ni][4 * g], acc[mi][ni][4 * g + 1], acc[mi][ni][4 * g + 2],
-                  acc[mi][ni][4 * g + 3]};
+      for (int ni = 0; ni < NB; ++ni)
+        *reinterpret_cast<f32x4*>(&stage_f[(b * 16 + l15) * SLD + ni * 16 + g16 * 4]) =
+            acc[2 * mi + b][ni];
     __builtin_amdgcn_s_waitcnt(0xc07f);
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
@@ -736,7 +746,7 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmParams& p, const TileCoo
               p.dsp[((size_t)tc.e * p.M + m) * p.dsp_ld + (n >> 7)] = t;
           }
         }
-        if (mi + 1 < MB) {
+        if (mi + 1 < WM / 32) {
 #pragma unroll
           for (int e = 0; e < EQ; ++e) load_h(mi + 1, q0 + e);
         }
@@ -814,7 +824,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void gemm_dma_kernel(GemmParams 
   // dX 1.08 -> 1.04, and a step of 40 experts x 681 rows, d 1472, h 832 893 -> 869 us
   // (less than the share of padding: under the power limit padding is cheap).
   if constexpr ((OPT & OPT_TAILS) != 0) {
-    static_assert(BM == 256 && BN == 256 && WGM * WGN == 8, "tails of 256 x 256 tiles");
+    constexpr int NW = WGM * WGN;
+    static_assert(BM == 256 && BN == 256 && (NW == 4 || NW == 8), "tails of 256 x 256 tiles");
     const int left = tc.M - tc.m0;
     // a K-major operand's tiles are multiples of 128 wide (256 when gathered), and a
     // SwiGLU backward wave covers 128 columns
@@ -822,27 +833,27 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void gemm_dma_kernel(GemmParams 
     constexpr bool BWD = EPI == EPI_SWIGLU_BWD, FINE = ROWS && A_KC && !BWD;
     if constexpr (FINE) {
       if (left <= 64) {
-        gemm_dma_tile<64, 256, 2, 4, KSTEP, STAGES, A_KC, B_KC, EPI, OUT_F32, OPT>(p, tc, smem);
+        gemm_dma_tile<64, 256, NW / 4, 4, KSTEP, STAGES, A_KC, B_KC, EPI, OUT_F32, OPT>(p, tc, smem);
         return;
       }
     }
     if constexpr (ROWS) {
       if (left <= 128) {
-        constexpr int GM = BWD ? 4 : 2;
-        gemm_dma_tile<128, 256, GM, 8 / GM, KSTEP, STAGES, A_KC, B_KC, EPI, OUT_F32, OPT>(p, tc, smem);
+        constexpr int GM = BWD ? NW / 2 : 2;
+        gemm_dma_tile<128, 256, GM, NW / GM, KSTEP, STAGES, A_KC, B_KC, EPI, OUT_F32, OPT>(p, tc, smem);
         return;
       }
     }
     if constexpr (FINE && B_KC) {   // (a K-major B beside three row blocks would spill)
       if (left <= 192) {
-        gemm_dma_tile<192, 256, 2, 4, KSTEP, STAGES, A_KC, B_KC, EPI, OUT_F32, OPT>(p, tc, smem);
+        gemm_dma_tile<192, 256, 2, NW / 2, KSTEP, STAGES, A_KC, B_KC, EPI, OUT_F32, OPT>(p, tc, smem);
         return;
       }
     }
     if constexpr (COLS) {
       if (p.N - tc.n0 <= (EPI == EPI_SWIGLU ? 64 : 128)) {
         constexpr int GN = BWD ? 1 : 2;
-        gemm_dma_tile<256, 128, 8 / GN, GN, KSTEP, STAGES, A_KC, B_KC, EPI, OUT_F32, OPT>(p, tc, smem);
+        gemm_dma_tile<256, 128, NW / GN, GN, KSTEP, STAGES, A_KC, B_KC, EPI, OUT_F32, OPT>(p, tc, smem);
         return;
       }
     }
@@ -893,7 +904,7 @@ hipError_t run_dma_var(GemmParams p, long max_rows, hipStream_t st) {
 
 // Row blocks of the forward expert products: 192 when they pad the expert
 // buffers enough less than blocks of 256 (one 2048-token sequence at c(t) =
-// 12 - 8t has 373 rows per expert: 384 computed instead of 512).  A 192-row tile (96 x 64
+// 12 - 8t has 373 rows per expert: 384 computed instead of 512).  A 192-row tile (96 x 128
 // per wave) does three quarters of a 256-row tile's work in 0.875 of its time, so a
 // computed row costs 7/6 as much.  Every choice keeps an expert's row blocks side by
 // side on one XCD, so its weights are fetched once.
@@ -982,7 +993,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_f32_kernel(GemmParams p) 
   for (int q = 0; q < AL; ++q) {
     const int id = (wave * AL + q) * 64 + lane;
     if constexpr (A_KC) {
-      const int row = id >> 3, lc = (id & 7) ^ kc_swz<64>(row);
+      const int row = id >> 3, lc = (id & 7) ^ kc_swz(row);
       int r = m0 + row;
       r = r < M ? r : M - 1;
       a_src[q] = p.a_rows ? (const float*)p.A +
@@ -998,7 +1009,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_f32_kernel(GemmParams p) 
   for (int q = 0; q < BL; ++q) {
     const int id = (wave * BL + q) * 64 + lane;
     if constexpr (B_KC) {
-      const int row = id >> 3, lc = (id & 7) ^ kc_swz<64>(row);
+      const int row = id >> 3, lc = (id & 7) ^ kc_swz(row);
       if constexpr (EPI == EPI_SWIGLU) {
         int r = n0 + row % (BN / 2);
         r = r < p.N ? r : p.N - 1;
@@ -1047,7 +1058,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_f32_kernel(GemmParams p) 
     if constexpr (decltype(kc)::value) {
       const int row = base + l31;
       return *reinterpret_cast<const f32x4*>(tile + row * (FK * 4) +
-                                             (((2 * s + half) ^ kc_swz<64>(row)) << 4));
+                                             (((2 * s + half) ^ kc_swz(row)) << 4));
     } else {
       const float* c = reinterpret_cast<const float*>(tile) + (8 * s + 4 * half) * width + base + l31;
       return f32x4{c[0], c[width], c[2 * width], c[3 * width]};
@@ -1261,13 +1272,13 @@ hipError_t launch_gemm_w13(int dtype, const void* Xe, const void* W1, const void
   }
   if (shared) {
     if (rows) return hipErrorInvalidValue;   // the shared experts read X as is
-    return run_dma<256, 256, 2, 4, 64, 2, true, true, EPI_SWIGLU, false, G_SH_W13>(p, st);
+    return run_dma<256, 256, 2, 2, 64, 2, true, true, EPI_SWIGLU, false, G_SH_W13>(p, st);
   }
   switch (fwd_block_rows(M)) {
     case 64: return run_dma<64, 128, 2, 2, 64, 3, true, true, EPI_SWIGLU, false, G_W13>(p, st);
     case 128: return run_dma<128, 128, 2, 2, 64, 3, true, true, EPI_SWIGLU, false, G_W13>(p, st);
-    case 192: return run_dma<192, 256, 2, 4, 64, 2, true, true, EPI_SWIGLU, false, G_W13>(p, st);
-    default: return run_dma<256, 256, 2, 4, 64, 2, true, true, EPI_SWIGLU, false, G_W13, OPT_TAILS>(p, st);
+    case 192: return run_dma<192, 256, 2, 2, 64, 2, true, true, EPI_SWIGLU, false, G_W13>(p, st);
+    default: return run_dma<256, 256, 2, 2, 64, 2, true, true, EPI_SWIGLU, false, G_W13, OPT_TAILS>(p, st);
   }
 }
 
@@ -1280,12 +1291,12 @@ hipError_t launch_gemm_w2(int dtype, const void* A, const void* W2, void* O, int
   p.C = O; p.c_bs = (long)M * d; p.ldc = d;
   if (M == 0) return hipSuccess;
   if (dtype == DT_F32) return run_f32<true, true, EPI_STORE>(p, st);
-  if (shared) return run_dma<256, 256, 4, 2, 64, 2, true, true, EPI_STORE, false, G_SH_W2>(p, st);
+  if (shared) return run_dma<256, 256, 2, 2, 64, 2, true, true, EPI_STORE, false, G_SH_W2>(p, st);
   switch (fwd_block_rows(M)) {
     case 64: return run_dma<64, 128, 2, 2, 64, 3, true, true, EPI_STORE, false, G_W2>(p, st);
     case 128: return run_dma<128, 256, 2, 4, 64, 3, true, true, EPI_STORE, false, G_W2>(p, st);
-    case 192: return run_dma<192, 256, 2, 4, 64, 2, true, true, EPI_STORE, false, G_W2>(p, st);
-    default: return run_dma<256, 256, 4, 2, 64, 2, true, true, EPI_STORE, false, G_W2, OPT_TAILS>(p, st);
+    case 192: return run_dma<192, 256, 2, 2, 64, 2, true, true, EPI_STORE, false, G_W2>(p, st);
+    default: return run_dma<256, 256, 2, 2, 64, 2, true, true, EPI_STORE, false, G_W2, OPT_TAILS>(p, st);
   }
 }
 
@@ -1514,7 +1525,7 @@ hipError_t launch_gemm_w13_var(int dtype, const void* Xe, const void* W1, const 
   p.var_rows = rows; p.var_tiles = tiles;
   if (max_rows == 0) return hipSuccess;
   if (dtype == DT_F32) return run_f32<true, true, EPI_SWIGLU>(p, st);
-  return run_dma_var<256, 256, 2, 4, 64, 2, true, true, EPI_SWIGLU, false, G_TC_W13, OPT_TAILS>(
+  return run_dma_var<256, 256, 2, 2, 64, 2, true, true, EPI_SWIGLU, false, G_TC_W13, OPT_TAILS>(
       p, max_rows, st);
 }
 
@@ -1529,7 +1540,7 @@ hipError_t launch_gemm_w2_var(int dtype, const void* A, const void* W2, void* O,
   p.var_rows = rows; p.var_tiles = tiles;
   if (max_rows == 0) return hipSuccess;
   if (dtype == DT_F32) return run_f32<true, true, EPI_STORE>(p, st);
-  return run_dma_var<256, 256, 4, 2, 64, 2, true, true, EPI_STORE, false, G_TC_W2, OPT_TAILS>(
+  return run_dma_var<256, 256, 2, 2, 64, 2, true, true, EPI_STORE, false, G_TC_W2, OPT_TAILS>(
       p, max_rows, st);
 }
 

@@ -221,6 +221,17 @@ def test_single_row_block_buffers(k, d, h):
     full_case(wl, inp=inp)
 
 
+@pytest.mark.parametrize("n,k,E", [(193, 65, 3), (321, 127, 9), (1021, 190, 17), (2049, 1985, 1)])
+def test_ragged_contractions(n, k, E):
+    # every weight gradient's last k-step is short (expert rows, all tokens, a router
+    # whose width is no multiple of 8): the rows past its end count as zero
+    wl = synth.small(f"ragged{k}", [n], 192, E, 128, seed=48, capacity_factor=k * E / n,
+                     backward=True, d_shared=192)
+    inp = synth.draw(wl, with_dy=True)
+    assert int(np.sum(caps_for(wl, inp))) == k
+    full_case(wl, inp=inp)
+
+
 def test_zero_capacity_everywhere():
     wl = synth.small("k0", [100, 50], 64, 8, 64, seed=14, capacity_factor=0.0, backward=True)
     out = full_case(wl)
