@@ -142,10 +142,13 @@ __device__ __forceinline__ void dma16(const void* g, void* lds) {
 // The same from a buffer resource: a uniform base, a 32-bit byte offset per lane and a
 // uniform one, so a K-contiguous operand's loads need one register each and no vector
 // arithmetic per step.
+// Operands end below BUF_BYTES (2^32 - 128, the library's limit); a load at BUF_PAST reads
+// zero.
+constexpr uint32_t BUF_BYTES = 0xffffff80u, BUF_PAST = 0xfffffff0u;
 #if defined(__HIP_DEVICE_COMPILE__)
 using Rsrc = __amdgpu_buffer_rsrc_t;
-__device__ __forceinline__ Rsrc make_rsrc(const void* base, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
+__device__ __forceinline__ Rsrc make_rsrc(const void* base) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, BUF_BYTES, 0x00020000);
 }
 __device__ __forceinline__ void dma16_buf(Rsrc r, uint32_t voff, int soff, void* lds) {
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 16,
@@ -153,13 +156,9 @@ __device__ __forceinline__ void dma16_buf(Rsrc r, uint32_t voff, int soff, void*
 }
 #else
 using Rsrc = int;
-__device__ inline Rsrc make_rsrc(const void*, uint32_t) { return 0; }
+__device__ inline Rsrc make_rsrc(const void*) { return 0; }
 __device__ inline void dma16_buf(Rsrc, uint32_t, int, void*) {}
 #endif
-
-// sizes of buffers that are never read past their end (at most 2^32 - 128 bytes, the
-// library's limit), and an offset past any of them
-constexpr uint32_t BUF_ALL = 0xffffff80u, BUF_PAST = 0xfffffff0u;
 
 constexpr int vmcnt_imm(int n) { return (n & 15) | (((n >> 4) & 3) << 14) | (7 << 4) | (15 << 8); }
 
@@ -321,15 +320,8 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmParams& p, const TileCoo
   }
   // a SwiGLU wave's rows all lie in W1 or all in W3
   static_assert(EPI != EPI_SWIGLU || (BN / 2) % (OB::LOADS * 8) == 0, "one weight per wave");
-  const Rsrc a_rsrc =
-      make_rsrc((A_KC ? p.a_rows != nullptr : GA) ? p.A : (const void*)Ab,
-                A_KC || GA ? BUF_ALL : (uint32_t)p.kv_a * (uint32_t)p.lda * 2u);
-  const Rsrc b_rsrc =
-      make_rsrc(EPI == EPI_SWIGLU && wave * OB::LOADS * 8 >= BN / 2 ? B2b : Bb,
-                B_KC || GB ? BUF_ALL
-                           : (uint32_t)(p.kv_b < p.k_split ? p.kv_b : p.k_split) * (uint32_t)p.ldb * 2u);
-  // K-major B split at k_split (a multiple of the k-step): steps from there on read B2
-  const Rsrc b2_rsrc = make_rsrc(!B_KC && B2b ? B2b : Bb, BUF_ALL);
+  const Rsrc a_rsrc = make_rsrc((A_KC ? p.a_rows != nullptr : GA) ? p.A : (const void*)Ab);
+  const Rsrc b_rsrc = make_rsrc(EPI == EPI_SWIGLU && wave * OB::LOADS * 8 >= BN / 2 ? B2b : Bb);
   // Issues k-step kt; the calls come with kt = 0, 1, 2, ... in order.
   // Loads [lo, hi) of k-step kt (A's loads first, then B's); each load of a
   // k-step is issued exactly once and the k-steps in order.
@@ -358,6 +350,11 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmParams& p, const TileCoo
       else
         km_load(a_rsrc, a_off[q], ((wave * OA::LOADS + q) * 64 + lane) / OA::CPR, kt * KSTEP, p.kv_a, p.lda, lds);
     }
+    // K-major B split at k_split (a multiple of the k-step): steps from there on read B2
+    // (selected, not branched to: a branch would split the interleaved group)
+    const bool second = !B_KC && !GB && kt * KSTEP >= p.k_split;
+    const int bk0 = kt * KSTEP - (second ? p.k_split : 0), bkv = p.kv_b - (second ? p.k_split : 0);
+    const Rsrc bk_rsrc = make_rsrc(second ? B2b : Bb);
     if constexpr (GA) {   // every A load of step kt has gone out: rows of step kt + 1
       if (lo < OA::LOADS && hi >= OA::LOADS)
         a_kidx = FIRST ? a_kidx1 : k_row(p.ka_rows, (kt + 1) * KSTEP + lane, p.kv_a);
@@ -372,10 +369,7 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmParams& p, const TileCoo
         dma16_buf(b_rsrc, b_off[q] + (uint32_t)pick_row(b_kidx, wave * OB::LOADS + q) * (uint32_t)p.ldb * 2u, 0, lds);
       } else {
         const int row = ((wave * OB::LOADS + q) * 64 + lane) / OB::CPR;
-        if (kt * KSTEP < p.k_split)
-          km_load(b_rsrc, b_off[q], row, kt * KSTEP, p.kv_b, p.ldb, lds);
-        else
-          km_load(b2_rsrc, b_off[q], row, kt * KSTEP - p.k_split, p.kv_b - p.k_split, p.ldb, lds);
+        km_load(bk_rsrc, b_off[q], row, bk0, bkv, p.ldb, lds);
       }
     }
     if constexpr (GB) {
