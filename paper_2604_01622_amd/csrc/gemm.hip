@@ -27,11 +27,13 @@
 // flight, lgkmcnt(0), before each use; with buffer loads it counts), and four waves
 // where both operands are K-contiguous.  K-major operands keep eight: their fragments
 // take twice the reads, and one wave per SIMD leaves those exposed (dW1/dW3 of one
-// 2048-token sequence 204 us against 235).  Measured on one card, 64 experts x 2071
+// 2048-token sequence 207 us against 226).  Measured on one card, 64 experts x 2071
 // rows, d 2048, h 1024, against 32x32x16 MFMAs, eight waves and global loads: W1/W3 1053
-// -> 1015 us, W2 532 -> 542, dA 642 -> 630, dW2 512 -> 461, dXe 1015 -> 983, dW1/dW3 1043
-// -> 899 within a step that as a whole goes 5127 -> 4853 (the kernels share one power
-// budget); one 2048-token sequence 916 -> 871 us.
+// -> 1008 us, W2 532 -> 533, dA 642 -> 608, dW2 512 -> 450, dX 1015 -> 934, dW1/dW3 1043
+// -> 906 (the kernels share one power budget), 1.2 PFLOP/s over the six where a loop of
+// nothing but MFMAs sustains 1.6 on such data; the step 5127 -> 4770.  128 x 128 tiles,
+// two workgroups a CU, for the weight gradients of few rows are slower (256 rows: dW1/dW3
+// 207 -> 252), as are four row blocks per tile group (one sequence's step 870 -> 887).
 //
 // The products that read the selected tokens' rows (of X, or of the output
 // gradient dY) gather them in the operand load: the W1/W3 and dA products per
@@ -494,11 +496,16 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmParams& p, const TileCoo
   // a refill's second half) run in separate straight-line segments, so that no branch
   // splits an interleaved group.
   constexpr int RA = MH * (A_KC ? 1 : 2), RB = NH * (B_KC ? 1 : 2);   // read instructions
-  // A stage's refill is issued in two parts: DMA_HEAD loads after the barrier
-  // that frees the stage, the rest in the next step's first sub-step (two
-  // stages only: the wait at every step end is then for all outstanding loads).
+  // A stage's refill is issued in two parts: DMA_HEAD loads after the barrier that frees
+  // the stage, the rest in the next step's first sub-step (two stages only: the wait at
+  // every step end is then for all outstanding loads).  K-major fragment reads leave
+  // room for half of it after the barrier; K-contiguous ones, half as many, for three
+  // quarters (against half: one 2048-token sequence's forward 357 -> 349 us, 4 x 4096
+  // tokens 1250 -> 1244, a step of 8 x 2048 4795 -> 4770; all of it: 345, 1280, 4828;
+  // K-major with three quarters: dW2 450 -> 473, dW1/dW3 897 -> 923).
   constexpr bool SPLIT_DMA = STAGES == 2;
-  constexpr int DMA_HEAD = SPLIT_DMA ? LOADS / 2 : LOADS, DMA_Q3 = DMA_HEAD / 2;
+  constexpr int DMA_HEAD = !SPLIT_DMA ? LOADS : (EARLY ? LOADS * 3 / 4 : LOADS / 2);
+  constexpr int DMA_Q3 = DMA_HEAD / 2;
   // orders a quadrant: after each MFMA its share of the LDS reads and DMA loads
   auto order = [&](auto reads, auto dmas) {
     constexpr int RD = decltype(reads)::value, DM = decltype(dmas)::value;
