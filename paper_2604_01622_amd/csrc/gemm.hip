@@ -144,8 +144,10 @@ __device__ __forceinline__ void dma16(const void* g, void* lds) {
 // The same from a buffer resource: a uniform base, a 32-bit byte offset per lane and a
 // uniform one, so a K-contiguous operand's loads need one register each and no vector
 // arithmetic per step.
-// Operands end below BUF_BYTES (2^32 - 128, the library's limit); a load at BUF_PAST reads
-// zero.
+// What a base reaches ends below BUF_BYTES: an ungathered K-contiguous A starts at its
+// tile's first row, so its offsets span one tile however many rows there are (the router's
+// dZ, [N, E rounded up to 64], passes 2^32 bytes); X and dY, read gathered, are below 2^31
+// bytes (N 2 d < 2^31 elements); run_dma checks the others.  A load at BUF_PAST reads zero.
 constexpr uint32_t BUF_BYTES = 0xffffff80u, BUF_PAST = 0xfffffff0u;
 #if defined(__HIP_DEVICE_COMPILE__)
 using Rsrc = __amdgpu_buffer_rsrc_t;
@@ -247,9 +249,9 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmParams& p, const TileCoo
 
   // ---- DMA sources.  Load q of a thread fills 1 KiB block (wave*L + q) of
   // the operand's stage area: 64 chunks, lane -> chunk.
-  // Every load has one byte offset from its operand's uniform base (an operand is
-  // below 2^32 bytes), the step's offset being uniform.  K-contiguous: the chunk in its
-  // row (clamped: rows past the end produce outputs that are not stored).
+  // Every load has one byte offset from a uniform base (see BUF_BYTES), the step's offset
+  // being uniform.  K-contiguous: the chunk in its row (clamped: rows past the end produce
+  // outputs that are not stored), an ungathered A from row m0 on.
   // K-major: the chunk at k-step 0, its column clamped into the operand likewise; rows
   // past the valid K ask for an offset past the buffer, which reads as zero.
   // K-major gathered (OPT_GA / OPT_GB): the chunk's column; the source rows of
@@ -298,7 +300,7 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmParams& p, const TileCoo
         const int tok = p.a_rows[(size_t)e * p.a_rows_bs + tc.row0 + r];
         a_off[q] = ((uint32_t)tok * (uint32_t)p.lda + lc * 8) * 2;
       } else {
-        a_off[q] = ((uint32_t)r * (uint32_t)p.lda + lc * 8) * 2;
+        a_off[q] = ((uint32_t)(r - m0) * (uint32_t)p.lda + lc * 8) * 2;
       }
     } else {
       const int row = id / OA::CPR, lc = (id % OA::CPR) ^ km_swz(row);
@@ -322,7 +324,8 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmParams& p, const TileCoo
   }
   // a SwiGLU wave's rows all lie in W1 or all in W3
   static_assert(EPI != EPI_SWIGLU || (BN / 2) % (OB::LOADS * 8) == 0, "one weight per wave");
-  const Rsrc a_rsrc = make_rsrc((A_KC ? p.a_rows != nullptr : GA) ? p.A : (const void*)Ab);
+  const bf16_t* const a_base = Ab + (A_KC ? (size_t)m0 * p.lda : 0);
+  const Rsrc a_rsrc = make_rsrc((A_KC ? p.a_rows != nullptr : GA) ? p.A : (const void*)a_base);
   const Rsrc b_rsrc = make_rsrc(EPI == EPI_SWIGLU && wave * OB::LOADS * 8 >= BN / 2 ? B2b : Bb);
   // Issues k-step kt; the calls come with kt = 0, 1, 2, ... in order.
   // Loads [lo, hi) of k-step kt (A's loads first, then B's); each load of a
@@ -862,6 +865,14 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void gemm_dma_kernel(GemmParams 
   gemm_dma_tile<BM, BN, WGM, WGN, KSTEP, STAGES, A_KC, B_KC, EPI, OUT_F32, OPT>(p, tc, smem);
 }
 
+// The operands that a tile addresses from their batch's start are within BUF_BYTES.
+template <bool A_KC, bool B_KC, int OPT>
+bool operands_in_reach(const GemmParams& p) {
+  const long a = (A_KC || (OPT & OPT_GA)) ? 0 : 2L * p.kv_a * p.lda;
+  const long b = (OPT & OPT_GB) ? 0 : 2L * (B_KC ? p.N : p.kv_b) * p.ldb;
+  return a <= (long)BUF_BYTES && b <= (long)BUF_BYTES;
+}
+
 // OPT: the options of the instantiation; the pointers of each option must be
 // set exactly when it is.
 template <int BM, int BN, int WGM, int WGN, int KSTEP, int STAGES, bool A_KC, bool B_KC, int EPI,
@@ -870,6 +881,7 @@ hipError_t run_dma(GemmParams p, hipStream_t st) {
   if (((OPT & OPT_GA) != 0) != (p.ka_rows != nullptr) ||
       ((OPT & OPT_GB) != 0) != (p.kb_rows != nullptr))
     return hipErrorInvalidValue;
+  if (!operands_in_reach<A_KC, B_KC, OPT>(p)) return hipErrorInvalidValue;
   p.MT = (p.M + BM - 1) / BM;
   p.NT = (EPI == EPI_SWIGLU) ? (p.N + BN / 2 - 1) / (BN / 2) : (p.N + BN - 1) / BN;
   const long ntile = (long)p.batches * p.MT * p.NT;
@@ -893,6 +905,7 @@ hipError_t run_dma(GemmParams p, hipStream_t st) {
 template <int BM, int BN, int WGM, int WGN, int KSTEP, int STAGES, bool A_KC, bool B_KC, int EPI,
           bool OUT_F32, int TAG, int OPT>
 hipError_t run_dma_var(GemmParams p, long max_rows, hipStream_t st) {
+  if (!operands_in_reach<A_KC, B_KC, OPT>(p)) return hipErrorInvalidValue;
   p.MT = 0;
   p.NT = (EPI == EPI_SWIGLU) ? (p.N + BN / 2 - 1) / (BN / 2) : (p.N + BN - 1) / BN;
   const long ntile = ((max_rows + BM - 1) / BM + p.batches) * p.NT;

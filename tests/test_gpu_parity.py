@@ -294,6 +294,35 @@ def test_near_the_size_limit():
     assert all(v <= out_tol("bf16") for v in errs.values()), errs
 
 
+def test_router_gradient_past_4_gib():
+    """dZ [N, 256] in bf16 passes 2^32 bytes at 8388608 tokens: dX of a group of 700
+    tokens beyond that point, against the oracle on that group alone (groups are
+    independent in both directions)."""
+    lens, E, d, h = [32768] * 256 + [700], 193, 64, 64
+    caps = np.array([1] * 256 + [100], dtype=np.int32)
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    N, lo = int(off[-1]), int(off[-2])
+    assert lo * 256 * 2 >= 2 ** 32 and E * N < 2 ** 31
+    print(f"[case] router gradient of {N} tokens, {E} experts", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(61)
+
+    def draw(std, *shape):
+        return (torch.randn(shape, generator=gen, device="cuda") * std).to(torch.bfloat16)
+
+    X, dY, Wg = draw(1.0, N, d), draw(1.0, N, d), draw(0.25, E, d)
+    W1, W3, W2 = draw(0.125, E, h, d), draw(0.125, E, h, d), draw(0.125, E, d, h)
+    Y, saved = ec.forward(X, Wg, W1, W3, W2, off, caps, save=True)
+    dX = ec.backward(X, Wg, W1, W3, W2, dY, saved, off, caps)[0]
+    torch.cuda.synchronize()
+    P = ec.Problem.of(X, Wg, h, off, caps, 1.0, None)
+    sel = ec.saved_views(saved, P)["sel_token"][:, 256:].cpu().numpy() - lo
+    w = [host(t) for t in (Wg, W1, W3, W2)]
+    g = ref.backward_ref(host(X[lo:]), *w, host(dY[lo:]), [0, 700], [100], 1.0, sel_token=sel)
+    err = {"dX": rel_l2(host(dX[lo:]), g["dX"]), "Y": rel_l2(host(Y[lo:]), g["Y"])}
+    print("[errs]", {k: f"{v:.2e}" for k, v in err.items()}, flush=True)
+    assert all(v <= out_tol("bf16") for v in err.values()), err
+
+
 @pytest.mark.parametrize("lens,d,E,h,cf", [
     ([65], 64, 5, 64, 2.0),             # 64-wide tiles, one of them nearly empty
     ([257], 192, 17, 320, 3.0),         # ... column blocks past the width
