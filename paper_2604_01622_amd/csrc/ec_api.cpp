@@ -165,7 +165,7 @@ BwdWs carve_bwd(Carve& c, const Plan& P) {
   w.dsp = (float*)c.take((size_t)P.E * P.K * ec::dsp_parts(P.dtype, P.h) * 4);
   w.dH = c.take((size_t)P.E * P.K * 2 * P.h * P.esz);
   w.dZ = c.take((size_t)P.N * P.EP * P.esz);
-  w.splits = ec::router_dwg_splits(P.N, P.E, P.d);
+  w.splits = ec::router_dwg_splits(P.N, P.d);
   w.part = (float*)c.take((size_t)w.splits * P.E * P.d * 4);
   w.dHs = nullptr;
   w.spart = nullptr;

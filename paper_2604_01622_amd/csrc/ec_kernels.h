@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "row_split.h"
+
 namespace ec {
 
 enum { DT_F32 = 0, DT_BF16 = 1 };
@@ -54,11 +56,10 @@ hipError_t launch_router_dz(int dtype, const float* S, const float* dsp, int npa
 hipError_t launch_router_dx(int dtype, const void* dZ, const void* Wg, void* dX, int N, int E,
                             int EP, int d, hipStream_t st);
 
-// Router backward, part 3: dWg [E,d] fp32 = dZ^T X, split over the tokens into
-// `splits` partial sums (part [splits,E,d] fp32) added in a fixed order.
+// Router backward, part 3: dWg [E,d] fp32 = dZ^T X, split over the tokens into at most
+// `splits` (router_dwg_splits) partial sums (part [splits,E,d] fp32) added in a fixed order.
 hipError_t launch_router_dwg(int dtype, const void* dZ, const void* X, float* dWg, float* part,
                              int splits, int N, int E, int EP, int d, hipStream_t st);
-int router_dwg_splits(int N, int E, int d);
 
 // ---- grouped GEMMs over E experts (M = K rows per expert) ----
 
@@ -113,9 +114,8 @@ hipError_t launch_coverage_drop(const int32_t* cnt, const GroupTable& tab, int32
 
 // Shared experts' weight gradients (one batch of N rows, K-major operands):
 // dW2 = dY^T A ([d,h]) and [dW1; dW3] = dH^T X ([h,d] each), split over the
-// rows into `splits` fp32 partials (part: splits * max(d*h, 2*h*d) floats)
+// rows into at most `splits` (wgrad_splits) fp32 partials (part: splits * max(d*h, 2*h*d) floats)
 // added in a fixed order.
-int wgrad_splits(int M, int N, int K);
 hipError_t launch_shared_dW2(int dtype, const void* dY, const void* A, void* dW2, int N, int d,
                              int h, float* part, int splits, hipStream_t st);
 hipError_t launch_shared_dW13(int dtype, const void* dH, const void* X, void* dW1, void* dW3,

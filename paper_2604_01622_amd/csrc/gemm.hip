@@ -1407,59 +1407,27 @@ hipError_t launch_router_dx(int dtype, const void* dZ, const void* Wg, void* dX,
   return run_dma<256, 256, 4, 2, 64, 2, true, false, EPI_STORE, false, G_ROUTER_DX>(p, st);
 }
 
-int router_dwg_splits(int N, int E, int d) {
-  (void)E;
-  int tiles = (d + 127) / 128;
-  int s = (512 + tiles - 1) / tiles;
-  int maxs = (N + 255) / 256;
-  if (s > maxs) s = maxs;
-  return s < 1 ? 1 : s;
-}
-
 hipError_t launch_router_dwg(int dtype, const void* dZ, const void* X, float* dWg, float* part,
                              int splits, int N, int E, int EP, int d, hipStream_t st) {
-  // dWg[j, n] = sum_i dZ[i, j] X[i, n], split over i in `splits` chunks
+  // dWg[j, n] = sum_i dZ[i, j] X[i, n], split over i in at most `splits` chunks
   if (N == 0 || splits < 1) return launch_zero(dWg, (size_t)E * d * sizeof(float), st);
-  const int chunk = (N + splits - 1) / splits;
-  GemmParams p = base_params();
-  p.A = dZ; p.a_bs = (long)chunk * EP; p.lda = EP;
-  p.B = X; p.b_bs = (long)chunk * d; p.ldb = d;
-  p.M = E; p.N = d; p.K = chunk; p.batches = splits;
-  p.C = part; p.c_bs = (long)E * d; p.ldc = d;
-  // each split sees rows [s*chunk, min(N, (s+1)*chunk)); the last may be short
-  const int last = N - (splits - 1) * chunk;
-  hipError_t err;
-  if (last == chunk) {
-    p.kv_a = chunk; p.kv_b = chunk;
-    if (dtype == DT_F32) err = run_f32<false, false, EPI_STORE>(p, st);
-    else err = run_dma<128, 256, 2, 4, 64, 2, false, false, EPI_STORE, true, G_ROUTER_DWG>(p, st);
-  } else {
-    GemmParams p1 = p;
-    p1.batches = splits - 1; p1.kv_a = chunk; p1.kv_b = chunk;
-    err = (splits > 1) ? ((dtype == DT_F32) ? run_f32<false, false, EPI_STORE>(p1, st)
-                                            : run_dma<128, 256, 2, 4, 64, 2, false, false, EPI_STORE, true, G_ROUTER_DWG>(p1, st))
-                       : hipSuccess;
-    if (err != hipSuccess) return err;
-    GemmParams p2 = p;
-    const long ao = (long)(splits - 1) * p.a_bs, bo = (long)(splits - 1) * p.b_bs;
-    p2.A = (const char*)p.A + ao * ((dtype == DT_F32) ? 4 : 2);
-    p2.B = (const char*)p.B + bo * ((dtype == DT_F32) ? 4 : 2);
-    p2.C = part + (size_t)(splits - 1) * E * d;
-    p2.batches = 1; p2.kv_a = last; p2.kv_b = last;
-    err = (dtype == DT_F32) ? run_f32<false, false, EPI_STORE>(p2, st)
-                            : run_dma<128, 256, 2, 4, 64, 2, false, false, EPI_STORE, true, G_ROUTER_DWG>(p2, st);
-  }
+  const RowSplit rs = split_rows(N, splits, 1);
+  const size_t esz = dtype == DT_F32 ? 4 : 2;
+  // `batches` chunks from row `row0` on, of which `rows` rows each are there
+  auto run = [&](int batches, long row0, int rows, float* out) -> hipError_t {
+    GemmParams p = base_params();
+    p.A = (const char*)dZ + row0 * EP * esz; p.a_bs = (long)rs.chunk * EP; p.lda = EP;
+    p.B = (const char*)X + row0 * d * esz; p.b_bs = (long)rs.chunk * d; p.ldb = d;
+    p.M = E; p.N = d; p.K = rs.chunk; p.kv_a = rows; p.kv_b = rows; p.batches = batches;
+    p.C = out; p.c_bs = (long)E * d; p.ldc = d;
+    if (dtype == DT_F32) return run_f32<false, false, EPI_STORE>(p, st);
+    return run_dma<128, 256, 2, 4, 64, 2, false, false, EPI_STORE, true, G_ROUTER_DWG>(p, st);
+  };
+  hipError_t err = rs.full > 0 ? run(rs.full, 0, rs.chunk, part) : hipSuccess;
+  if (err == hipSuccess && rs.last > 0)
+    err = run(1, (long)rs.full * rs.chunk, rs.last, part + (size_t)rs.full * E * d);
   if (err != hipSuccess) return err;
-  return run_splitk_store<float>(part, splits, E, d, E, dWg, dWg, d, st);
-}
-
-int wgrad_splits(int M, int N, int K) {
-  // one tile per CU: every further split writes and reads another M x N fp32 partial
-  const int tiles = ((M + 255) / 256) * ((N + 255) / 256);
-  int s = (256 + tiles - 1) / tiles;
-  const int maxs = (K + 255) / 256;
-  if (s > maxs) s = maxs;
-  return s < 1 ? 1 : s;
+  return run_splitk_store<float>(part, rs.parts(), E, d, E, dWg, dWg, d, st);
 }
 
 namespace {
@@ -1477,10 +1445,8 @@ hipError_t run_wgrad_splitk(const void* A, int lda, const void* B, int ldb, int 
     if (e != hipSuccess || c_split >= M) return e;
     return launch_zero(C2, (size_t)(M - c_split) * ldc * 2, st);
   }
-  const int chunk = ((K + splits - 1) / splits + 63) / 64 * 64;
-  const int full = K / chunk;                 // splits with chunk rows
-  const int last = K - full * chunk;          // rows of the final short split (may be 0)
-  const int nsplit = full + (last > 0 ? 1 : 0);
+  const RowSplit rs = split_rows(K, splits, 64);
+  const int chunk = rs.chunk, full = rs.full, last = rs.last;
   GemmParams p = base_params();
   p.A = A; p.a_bs = (long)chunk * lda; p.lda = lda;
   p.B = B; p.b_bs = (long)chunk * ldb; p.ldb = ldb;
@@ -1501,7 +1467,7 @@ hipError_t run_wgrad_splitk(const void* A, int lda, const void* B, int ldb, int 
     err = run_dma<256, 256, 4, 2, 64, 2, false, false, EPI_STORE, true, TAG>(q, st);
     if (err != hipSuccess) return err;
   }
-  return run_splitk_store<bf16_t>(part, nsplit, M, N, c_split, (bf16_t*)C, (bf16_t*)C2, ldc, st);
+  return run_splitk_store<bf16_t>(part, rs.parts(), M, N, c_split, (bf16_t*)C, (bf16_t*)C2, ldc, st);
 }
 
 }  // namespace

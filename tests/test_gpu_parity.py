@@ -294,6 +294,16 @@ def test_near_the_size_limit():
     assert all(v <= out_tol("bf16") for v in errs.values()), errs
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n", [131073, 131327])
+def test_router_gradient_of_fewer_splits_than_planned(n, dtype):
+    # 512 planned splits of the tokens: chunks of 257 rows make 510 and a rest of 3,
+    # or 511 and none
+    wl = synth.small(f"splits{n}", [n], 64, 3, 64, dtype=dtype, seed=60, capacity_factor=3e-3,
+                     backward=True)
+    full_case(wl)
+
+
 def test_router_gradient_past_4_gib():
     """dZ [N, 256] in bf16 passes 2^32 bytes at 8388608 tokens: dX of a group of 700
     tokens beyond that point, against the oracle on that group alone (groups are
