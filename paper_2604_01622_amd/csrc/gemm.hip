@@ -967,7 +967,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_f32_kernel(GemmParams p) 
   static_assert(!(GA && A_KC) && (OPT & ~OPT_GA) == 0, "a K-major A may be gathered");
   __shared__ __attribute__((aligned(1024))) char smem[2 * STAGE_BYTES];
 
-  const int t = xcd_tile_id(blockIdx.x, gridDim.x);
+  const int t = xcd_tile_id(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
   const int per_b = p.MT * p.NT;
   if (t >= p.batches * per_b) return;
   const int e = t / per_b, rem = t - e * per_b;
@@ -1204,10 +1204,14 @@ hipError_t launch_f32_tile(GemmParams p, hipStream_t st) {
   p.NT = (EPI == EPI_SWIGLU) ? (p.N + BN / 2 - 1) / (BN / 2) : (p.N + BN - 1) / BN;
   const long ntile = (long)p.batches * p.MT * p.NT;
   if (ntile == 0) return hipSuccess;
-  if (ntile >= (1l << 31) - 8) return hipErrorInvalidValue;
-  const long grid = (ntile + 7) / 8 * 8;
+  if (ntile >= (1l << 30)) return hipErrorInvalidValue;   // 2^26 at the size limits
+  // One dimension of a launch ends below 2^32 threads, which token choice passes (its
+  // grid covers every token for every expert): rows of at most 2^23 workgroups, whole
+  // rounds of the XCDs each.
+  const long rows = (ntile + (1l << 23) - 1) >> 23;
+  const long per_row = ((ntile + rows - 1) / rows + 7) / 8 * 8;
   gemm_f32_kernel<BM, BN, WGM, WGN, A_KC, B_KC, EPI, OPT>
-      <<<dim3((unsigned)grid), 64 * WGM * WGN, 0, st>>>(p);
+      <<<dim3((unsigned)per_row, (unsigned)rows), 64 * WGM * WGN, 0, st>>>(p);
   return hipGetLastError();
 }
 

@@ -724,6 +724,32 @@ def test_tc_f32():
     check_tc(inp, ec.tc_capacity(wl.group_lengths, 8, 2, 1.0), 2)
 
 
+def test_tc_f32_grid_past_2_32_threads():
+    """Dropless fp32 token choice whose grid (every expert may take every token) holds
+    2^24 tiles of 256 threads, one dimension of a launch ending below 2^32: sampled
+    tokens against the chosen expert's SwiGLU in float64 (top 1: gate 1)."""
+    N, E, d, h = 32768, 256, 64, 16384
+    assert E * (N // 128) * (2 * h // 128) * 256 >= 2 ** 32
+    print(f"[case] fp32 token choice N={N} E={E} d={d} h={h}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(62)
+
+    def draw(std, *shape):
+        return torch.randn(shape, generator=gen, device="cuda") * std
+
+    X, Wg = draw(1.0, N, d), draw(0.125, E, d)
+    W1, W3, W2 = draw(0.125, E, h, d), draw(0.125, E, h, d), draw(0.0078125, E, d, h)
+    off, cap = [0, N], ec.tc_capacity([N], E, 1, 0.0)
+    Y, rows = ec.tc_forward(X, Wg, W1, W3, W2, off, cap, 1)
+    torch.cuda.synchronize()
+    assert int(rows[-1]) == N
+    for i in (0, 1, 127, 128, 9999, 16384, 32766, 32767):
+        x = X[i].double()
+        j = int(torch.argmax(Wg.double() @ x))
+        h1, h3 = W1[j].double() @ x, W3[j].double() @ x
+        y = W2[j].double() @ (h1 * torch.sigmoid(h1) * h3)
+        assert rel_l2(host(Y[i]), y.cpu().numpy()) <= out_tol("f32"), i
+
+
 def test_tc_skewed_router_with_empty_experts():
     # router rows of very different norms: a few experts take most tokens and
     # some none at all (zero-row experts in the grouped GEMM)
