@@ -31,6 +31,7 @@ namespace {
 constexpr int TK_THREADS = 256;
 constexpr int TK_IPT = 8;                         // tokens per thread in the compaction pass
 constexpr int TK_TILE = TK_THREADS * TK_IPT;
+constexpr int TK_SHORT = 4096;                    // longest column of at most 8 waves
 
 __device__ __forceinline__ float key_to_f32(uint32_t k) {
   return __uint_as_float((k & 0x80000000u) ? (k ^ 0x80000000u) : ~k);
@@ -355,17 +356,17 @@ __global__ __launch_bounds__(TK_THREADS) void topk_kernel(const float* __restric
 
 }  // namespace
 
-hipError_t launch_topk(const float* ST, int N, int E, int K, const GroupTable& tab,
-                       int32_t* sel_token, float* sel_gate, int32_t* slotT, hipStream_t st) {
-  if (tab.n == 0 || E == 0) return hipSuccess;
-  int maxL = 0;
-  for (int g = 0; g < tab.n; ++g) maxL = tab.len[g] > maxL ? tab.len[g] : maxL;
+namespace {
+
+// One launch over the groups of `tab`, of at most maxL tokens.
+hipError_t run_topk(const float* ST, int N, int E, int K, const GroupTable& tab, int maxL,
+                    int32_t* sel_token, float* sel_gate, int32_t* slotT, hipStream_t st) {
   const dim3 grid(E, tab.n);
   if (maxL <= 512) {
     topk_col_kernel<8, 1><<<grid, 64, 0, st>>>(ST, N, K, tab, sel_token, sel_gate, slotT);
   } else if (maxL <= 2048) {
     topk_col_kernel<8, 4><<<grid, 256, 0, st>>>(ST, N, K, tab, sel_token, sel_gate, slotT);
-  } else if (maxL <= 4096) {
+  } else if (maxL <= TK_SHORT) {
     topk_col_kernel<8, 8><<<grid, 512, 0, st>>>(ST, N, K, tab, sel_token, sel_gate, slotT);
   } else if (maxL <= 8192) {
     topk_col_kernel<8, 16><<<grid, 1024, 0, st>>>(ST, N, K, tab, sel_token, sel_gate, slotT);
@@ -377,6 +378,44 @@ hipError_t launch_topk(const float* ST, int N, int E, int K, const GroupTable& t
     topk_kernel<<<grid, TK_THREADS, 0, st>>>(ST, N, E, K, tab, sel_token, sel_gate, slotT);
   }
   return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_topk(const float* ST, int N, int E, int K, const GroupTable& tab,
+                       int32_t* sel_token, float* sel_gate, int32_t* slotT, hipStream_t st) {
+  if (tab.n == 0 || E == 0) return hipSuccess;
+  int maxL = 0;
+  for (int g = 0; g < tab.n; ++g) maxL = tab.len[g] > maxL ? tab.len[g] : maxL;
+  // A launch takes the form that its longest group needs.  Up to 512 columns, two a CU,
+  // (nearly) every column runs at once and the longest sets the time, so one launch is best
+  // (9000 + 6000 + 100 tokens, 128 experts: 71 us in one, 78 in three); columns of up to
+  // TK_SHORT tokens take little either way.  Beyond that a short group in a long group's
+  // form keeps 16 waves of 8 to 32 keys a lane busy with nothing, so each form gets a
+  // launch of its own groups (routing of 20000 + 60 x 100 tokens, 128 experts: 711 us in
+  // one launch, 73 in two; 5000 + 60 x 300: 199 and 59; 32768 + 60 x 5000: 764 and 497).
+  if (maxL <= TK_SHORT || (long)E * tab.n <= 512)
+    return run_topk(ST, N, E, K, tab, maxL, sel_token, sel_gate, slotT, st);
+  int lo = -1;                                     // the launch's lengths: (lo, hi]
+  for (const int hi : {TK_SHORT, 8192, 16384, 32768, INT32_MAX}) {
+    GroupTable part;
+    part.n = 0;
+    maxL = 0;
+    for (int g = 0; g < tab.n; ++g) {
+      if (tab.len[g] <= lo || tab.len[g] > hi) continue;
+      const int n = part.n++;
+      part.off[n] = tab.off[g];
+      part.len[n] = tab.len[g];
+      part.k[n] = tab.k[g];
+      part.seg[n] = tab.seg[g];
+      maxL = tab.len[g] > maxL ? tab.len[g] : maxL;
+    }
+    lo = hi;
+    if (part.n == 0) continue;
+    const hipError_t e = run_topk(ST, N, E, K, part, maxL, sel_token, sel_gate, slotT, st);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace ec

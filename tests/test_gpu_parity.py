@@ -394,6 +394,14 @@ def test_topk_long_columns(lens, ties):
     test_topk_every_path(lens, ties)
 
 
+@pytest.mark.parametrize("ties", [False, True])
+def test_topk_a_launch_per_form(ties):
+    # more than 512 columns over groups of every form, an empty one among them, in no order
+    # of length: one launch each for up to 4096, 8192, 16384, 32768 tokens and beyond
+    lens = [100, 33000, 4096, 0, 8192, 4097, 17, 20000, 8193, 16384] + [60] * 70
+    test_topk_every_path(lens, ties)
+
+
 def test_ties_zero_router():
     # Wg = 0: every score is exactly 1/E and each expert takes the first k tokens
     wl = synth.small("ties", [64, 40], 64, 8, 64, seed=19, capacity_factor=2.0)
