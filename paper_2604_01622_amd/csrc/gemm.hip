@@ -232,11 +232,13 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmParams& p, const TileCoo
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave % WGM, wn = wave / WGM;
   // SwiGLU: the row factors of this wave's rows (lane l holds row wm*WM + 64 t
-  // + l), read before the main loop so the epilogue finds them in registers
+  // + l), read before the main loop so the epilogue finds them in registers (after it in
+  // the forward's eight-wave tiles, which have none to spare)
   constexpr bool GATED = EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_BWD;
+  constexpr bool LATE_GATE = EPI == EPI_SWIGLU && NT == 512;
   constexpr int GR = GATED ? (WM + 63) / 64 : 1;
   float gate_r[GR];
-  if constexpr (GATED) {
+  if constexpr (GATED && !LATE_GATE) {
 #pragma unroll
     for (int t = 0; t < GR; ++t) {
       const int m = m0 + wm * WM + 64 * t + lane;
@@ -596,6 +598,13 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmParams& p, const TileCoo
     }
     for (; kt < KT; ++kt) kstep(kt, F_{}, F_{}, F_{});
   }
+  if constexpr (LATE_GATE) {
+#pragma unroll
+    for (int t = 0; t < GR; ++t) {
+      const int m = m0 + wm * WM + 64 * t + lane;
+      gate_r[t] = (p.gate && m < M) ? p.gate[(size_t)e * p.gate_bs + m] : 1.f;
+    }
+  }
   __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
   __syncthreads();
 
@@ -933,6 +942,58 @@ int fwd_block_rows(int M) {
   if (M <= 128) return 128;
   const long r256 = (M + 255) / 256 * 256L, r192 = (M + 191) / 192 * 192L;
   return r192 * 7 < r256 * 6 ? 192 : 256;
+}
+
+// Waves of the forward products' 256- and 192-row tiles: four of 128 x 128 read a third
+// less LDS and draw less power, which pays while the chip is full for long; eight of 128 x
+// 64 share a tile's prologue and epilogue out further and hide more latency, which pays
+// where a contraction is short or the tiles fill half the chip once (kept to that for W2,
+// whose eight-wave stores are the slower on some cards: 64 experts x 256 rows, d 1024, h
+// 512, 256 tiles, 22.0 us in four and 26.5 in eight).  Measured, four against eight: W1/W3
+// of 64 experts x 2048 rows, d 2048, h 1024 847 and 872 us; d 1024, h 512 237 and 246 (512
+// rows 63.3 and 60.5); d 640, h 384, 1400 rows 105 and 97; d 512, h 256, 256 rows 19.6 and
+// 17.4; 32 experts, d 768, h 1536, 512 rows (768 tiles) 77.6 and 81.5; 8 experts, d 2048,
+// h 1024, 512 rows (128 tiles) 44.0 and 42.3, W2 there 27.4 and 26.2 (d 1024, h 512 17.4
+// and 16.2).
+bool fwd_eight_waves(int epi, long tiles, int k) {
+  if (tiles <= 128) return true;
+  return epi == EPI_SWIGLU && (k <= 704 || (k <= 1024 && tiles <= 512));
+}
+
+// A forward product in BM x 256 tiles of four or eight waves.
+template <int BM, int EPI, int TAG, int OPT, bool VAR = false>
+hipError_t run_fwd(const GemmParams& p, hipStream_t st, long max_rows = 0) {
+  constexpr int WIDTH = EPI == EPI_SWIGLU ? 128 : 256;   // output columns of a tile
+  // variable rows: the row blocks of max_rows in one and half a block more per batch
+  const long blocks = VAR ? max_rows / BM + (p.batches + 1) / 2
+                          : (long)p.batches * ((p.M + BM - 1) / BM);
+  const long tiles = blocks * ((p.N + WIDTH - 1) / WIDTH);
+  auto run = [&](auto wgn) -> hipError_t {
+    constexpr int WGN = decltype(wgn)::value;
+    if constexpr (VAR)
+      return run_dma_var<BM, 256, 2, WGN, 64, 2, true, true, EPI, false, TAG, OPT>(p, max_rows, st);
+    else
+      return run_dma<BM, 256, 2, WGN, 64, 2, true, true, EPI, false, TAG, OPT>(p, st);
+  };
+  return fwd_eight_waves(EPI, tiles, p.K) ? run(std::integral_constant<int, 4>{})
+                                          : run(std::integral_constant<int, 2>{});
+}
+
+// Buffers of one 128-row block (three stages): 128 x 128 tiles of four waves while there
+// is at most one per CU; 128 x 256 of eight, which read the rows half as often, where
+// those are at most one per CU.  Past that W1/W3 takes the narrow and W2 the wide ones, by
+// measurement alone.  128 rows, narrow against wide: W1/W3 of 64 experts, d 512, h 256 (256
+// narrow tiles) 10.5 and 12.4 us, d 1024, h 512 (512) 28.2 and 23.8, 24 experts, d 2048,
+// h 1024 (384) 49.6 and 41.9, 64 experts (1024) 127 and 131; W2 of 8 experts, d 2048, h
+// 1024 (128) 13.0 and 16.1, 64 experts (1024) 63 and 57.
+template <int EPI, int TAG>
+hipError_t run_fwd_128(const GemmParams& p, hipStream_t st) {
+  const int width = EPI == EPI_SWIGLU ? 2 * p.N : p.N;
+  const long narrow = (long)p.batches * ((width + 127) / 128);
+  const long wide = (long)p.batches * ((width + 255) / 256);
+  if (narrow <= 256 || (EPI == EPI_SWIGLU && wide > 256))
+    return run_dma<128, 128, 2, 2, 64, 3, true, true, EPI, false, TAG>(p, st);
+  return run_dma<128, 256, 2, 4, 64, 3, true, true, EPI, false, TAG>(p, st);
 }
 
 // ------------------------------------------------------------------ fp32 MFMA
@@ -1290,13 +1351,13 @@ hipError_t launch_gemm_w13(int dtype, const void* Xe, const void* W1, const void
   }
   if (shared) {
     if (rows) return hipErrorInvalidValue;   // the shared experts read X as is
-    return run_dma<256, 256, 2, 2, 64, 2, true, true, EPI_SWIGLU, false, G_SH_W13>(p, st);
+    return run_fwd<256, EPI_SWIGLU, G_SH_W13, 0>(p, st);
   }
   switch (fwd_block_rows(M)) {
     case 64: return run_dma<64, 128, 2, 2, 64, 3, true, true, EPI_SWIGLU, false, G_W13>(p, st);
-    case 128: return run_dma<128, 128, 2, 2, 64, 3, true, true, EPI_SWIGLU, false, G_W13>(p, st);
-    case 192: return run_dma<192, 256, 2, 2, 64, 2, true, true, EPI_SWIGLU, false, G_W13>(p, st);
-    default: return run_dma<256, 256, 2, 2, 64, 2, true, true, EPI_SWIGLU, false, G_W13, OPT_TAILS>(p, st);
+    case 128: return run_fwd_128<EPI_SWIGLU, G_W13>(p, st);
+    case 192: return run_fwd<192, EPI_SWIGLU, G_W13, 0>(p, st);
+    default: return run_fwd<256, EPI_SWIGLU, G_W13, OPT_TAILS>(p, st);
   }
 }
 
@@ -1309,12 +1370,12 @@ hipError_t launch_gemm_w2(int dtype, const void* A, const void* W2, void* O, int
   p.C = O; p.c_bs = (long)M * d; p.ldc = d;
   if (M == 0) return hipSuccess;
   if (dtype == DT_F32) return run_f32<true, true, EPI_STORE>(p, st);
-  if (shared) return run_dma<256, 256, 2, 2, 64, 2, true, true, EPI_STORE, false, G_SH_W2>(p, st);
+  if (shared) return run_fwd<256, EPI_STORE, G_SH_W2, 0>(p, st);
   switch (fwd_block_rows(M)) {
     case 64: return run_dma<64, 128, 2, 2, 64, 3, true, true, EPI_STORE, false, G_W2>(p, st);
-    case 128: return run_dma<128, 256, 2, 4, 64, 3, true, true, EPI_STORE, false, G_W2>(p, st);
-    case 192: return run_dma<192, 256, 2, 2, 64, 2, true, true, EPI_STORE, false, G_W2>(p, st);
-    default: return run_dma<256, 256, 2, 2, 64, 2, true, true, EPI_STORE, false, G_W2, OPT_TAILS>(p, st);
+    case 128: return run_fwd_128<EPI_STORE, G_W2>(p, st);
+    case 192: return run_fwd<192, EPI_STORE, G_W2, 0>(p, st);
+    default: return run_fwd<256, EPI_STORE, G_W2, OPT_TAILS>(p, st);
   }
 }
 
@@ -1509,8 +1570,7 @@ hipError_t launch_gemm_w13_var(int dtype, const void* Xe, const void* W1, const 
   p.var_rows = rows; p.var_tiles = tiles;
   if (max_rows == 0) return hipSuccess;
   if (dtype == DT_F32) return run_f32<true, true, EPI_SWIGLU>(p, st);
-  return run_dma_var<256, 256, 2, 2, 64, 2, true, true, EPI_SWIGLU, false, G_TC_W13, OPT_TAILS>(
-      p, max_rows, st);
+  return run_fwd<256, EPI_SWIGLU, G_TC_W13, OPT_TAILS, true>(p, st, max_rows);
 }
 
 hipError_t launch_gemm_w2_var(int dtype, const void* A, const void* W2, void* O, int E,
@@ -1524,8 +1584,7 @@ hipError_t launch_gemm_w2_var(int dtype, const void* A, const void* W2, void* O,
   p.var_rows = rows; p.var_tiles = tiles;
   if (max_rows == 0) return hipSuccess;
   if (dtype == DT_F32) return run_f32<true, true, EPI_STORE>(p, st);
-  return run_dma_var<256, 256, 2, 2, 64, 2, true, true, EPI_STORE, false, G_TC_W2, OPT_TAILS>(
-      p, max_rows, st);
+  return run_fwd<256, EPI_STORE, G_TC_W2, OPT_TAILS, true>(p, st, max_rows);
 }
 
 }  // namespace ec

@@ -221,6 +221,23 @@ def test_single_row_block_buffers(k, d, h):
     full_case(wl, inp=inp)
 
 
+@pytest.mark.parametrize("k,E,d,h", [
+    (790, 33, 1088, 320),    # four waves a tile (more than 128 tiles), last block of 22 rows
+    (850, 33, 1088, 320),    # ... of 82 rows
+    (430, 33, 1088, 320),    # ... of 174 rows
+    (361, 33, 1088, 320),    # ... 192-row blocks
+    (430, 40, 640, 320),     # short contraction: W1/W3 in eight waves, W2 in four
+    (100, 40, 1088, 448),    # one row block: the wide tiles of both products
+    (128, 72, 192, 1088),    # ... W1/W3 narrow past one round, W2 narrow
+])
+def test_forward_products_of_many_tiles(k, E, d, h):
+    wl = synth.small(f"many{k}", [1024], d, E, h, seed=49, capacity_factor=k * E / 1024,
+                     backward=True)
+    inp = synth.draw(wl, with_dy=True)
+    assert int(np.sum(caps_for(wl, inp))) == k
+    full_case(wl, inp=inp)
+
+
 @pytest.mark.parametrize("n,k,E", [(193, 65, 3), (321, 127, 9), (1021, 190, 17), (2049, 1985, 1)])
 def test_ragged_contractions(n, k, E):
     # every weight gradient's last k-step is short (expert rows, all tokens, a router
@@ -724,6 +741,12 @@ def test_tc_top1_odd_experts():
     wl = synth.small("tc1", [257, 100], 64, 17, 64, seed=51, capacity_factor=1.0)
     inp = synth.draw(wl)
     check_tc(inp, ec.tc_capacity(wl.group_lengths, 17, 1, 1.25), 1)
+
+
+def test_tc_many_tiles():
+    # four waves a tile in both products, every expert's last row block of its own height
+    wl = synth.small("tcmany", [2500, 1533], 1088, 33, 320, seed=55, capacity_factor=1.0)
+    check_tc(synth.draw(wl), ec.tc_capacity(wl.group_lengths, 33, 8, 0.0), 8)
 
 
 def test_tc_f32():
