@@ -201,18 +201,23 @@ __global__ __launch_bounds__(64 * TG * RouterCfg<ET>::KS) void router_softmax_bf
 
 // fp32 storage: plain fp32 FMA, two-level sums: each 32-wide K chunk of a logit in its
 // own running sum, the chunk sums added in K order (rounding error grows with the chunk
-// and chunk counts, not d).  TR tokens per workgroup; KC wide K tiles of X and Wg go
-// through LDS, the next tile's loads in flight behind the sums of this one.  The chunk
-// sums of a tile are shared out over all threads (a thread: one token, one chunk, four
-// experts) and then added in K order by the thread that owns the logit, so that a
-// few tokens and experts still fill a workgroup: latency bounds these sizes (2048
-// tokens x 16 experts, d 1024: 88 us with one thread per logit and 32 tokens per
-// workgroup).
-template <int KC, int TR>
+// and chunk counts, not d).  Eight tokens per workgroup, which fill the CUs from 2048
+// tokens on; KC wide K tiles of X and Wg go through LDS, the next tile's loads in flight
+// behind the sums of this one.  The chunk sums of a tile are shared out over all threads
+// (a thread: one token, one chunk, four experts) and then added in K order by the thread
+// that owns the logit, so that a few tokens and experts still fill a workgroup: latency
+// bounds these sizes (2048 tokens x 16 experts, d 1024: 88 us with one thread per logit
+// and 32 tokens per workgroup).  32 tokens per workgroup re-read Wg a quarter as often but
+// leave one or two workgroups a CU instead of three, and are no faster with many tokens
+// either (routing of 32768 tokens, d 1024: 32 experts 122 us with 8 and 197 with 32, 64
+// experts 218 and 221, 256 experts 639 and 694).
+constexpr int RF_TOK = 8;
+
+template <int KC>
 __global__ __launch_bounds__(256) void router_softmax_f32_kernel(
     const float* __restrict__ X, const float* __restrict__ Wg, float* __restrict__ S,
     float* __restrict__ ST, int N, int d, int E, float inv_tau) {
-  constexpr int KS = KC / 32, LD = KC + 4;
+  constexpr int TR = RF_TOK, KS = KC / 32, LD = KC + 4;
   constexpr int ME = KC == 256 ? 32 : (KC == 64 ? 128 : 256);   // most experts
   constexpr int QW = ME * KC / 4 / 256, QX = TR * KC / 4 / 256;   // 16-byte loads per thread
   constexpr int QO = TR * ME / 256;                               // logits per owner
@@ -322,12 +327,8 @@ __global__ __launch_bounds__(256) void router_softmax_f32_kernel(
 template <int KC>
 hipError_t run_router_f32(const float* x, const float* w, float* S, float* ST, int N, int d, int E,
                           float inv_tau, hipStream_t st) {
-  // 32 tokens per workgroup re-read the router matrix a quarter as often, once the
-  // tokens still fill every CU twice over; 8 fill the CUs from 2048 tokens on
-  if (N >= 2 * 256 * 32)
-    router_softmax_f32_kernel<KC, 32><<<(N + 31) / 32, 256, 0, st>>>(x, w, S, ST, N, d, E, inv_tau);
-  else
-    router_softmax_f32_kernel<KC, 8><<<(N + 7) / 8, 256, 0, st>>>(x, w, S, ST, N, d, E, inv_tau);
+  router_softmax_f32_kernel<KC><<<(N + RF_TOK - 1) / RF_TOK, 256, 0, st>>>(x, w, S, ST, N, d, E,
+                                                                          inv_tau);
   return hipGetLastError();
 }
 

@@ -365,7 +365,9 @@ def test_f32_product_tiles(lens, d, E, h, cf):
     ([9], 64, 1),              # less than one K tile, one token past a workgroup
     ([130], 320, 33),          # K tiles of 64 with 33 experts
     ([77], 448, 129),          # K tiles of 32
-    ([16380, 9], 192, 7),      # 32 tokens per workgroup, a partial K tile, a ragged end
+    ([16380, 9], 192, 7),      # 2049 workgroups, a partial K tile, a ragged end
+    ([16380, 9], 192, 33),     # ... K tiles of 64
+    ([16380, 9], 192, 129),    # ... and of 32
 ])
 def test_f32_router_tiles(lens, d, E):
     wl = synth.small("f32router", lens, d, E, 64, dtype="f32", seed=45, capacity_factor=1.0)
