@@ -72,7 +72,6 @@ def stage_of_kernel(name):
     if not m:
         for key, st in (("router_softmax", "router"), ("topk_col_kernel", "topk"),
                         ("topk_kernel", "topk"), ("router_dz_kernel", "router_dz"),
-                        ("splitk_reduce_kernel", "router_dwg_reduce"),
                         ("splitk_store_kernel<float>", "router_dwg_reduce")):
             if key in name:
                 return st

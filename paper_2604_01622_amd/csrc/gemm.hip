@@ -6,15 +6,16 @@
 // bf16: one pipelined kernel (gemm_dma_kernel) for every product of the
 // forward and backward.  v_mfma_f32_16x16x32_bf16 with fp32 accumulation; a
 // 256 x 256 output tile per workgroup (the forward products take 192-, 128- or 64-row
-// tiles when those pad short expert buffers less).  K advances 64 at a time through a
-// 2-stage LDS ring filled straight from global memory by buffer_load_dwordx4 ... lds
+// tiles when those pad short expert buffers less).  K advances 64 at a time through an LDS
+// ring of two stages (three for buffers of one short row block) filled straight from global memory by buffer_load_dwordx4 ... lds
 // (no VGPR staging, one offset register per load).  K-contiguous operands sit in LDS as
 // 128-byte rows with XOR-swizzled 16-byte chunks (conflict-free fragment reads);
 // K-major operands (the weight gradients' token-row contractions, and the weights in
 // the dA and dX products) stay K-major in LDS and are read with the transposing
 // ds_read_b64_tr_b16.  The MFMAs alternate with the next sub-step's fragment reads
-// and, once the barrier has freed a stage, with its refill's DMA (half of it then,
-// half in the next step), so LDS latency hides behind MFMAs in flight.  The MFMAs
+// and, once the barrier has freed a stage, with its refill's DMA (with two stages half of
+// it then, three quarters where both operands are K-contiguous, the rest in the next
+// step), so LDS latency hides behind MFMAs in flight.  The MFMAs
 // take the B fragment first, so each lane ends with four consecutive output columns
 // of a row, staged through LDS with 16-byte writes for coalesced stores.  Tiles are
 // numbered so that consecutive ones share an expert and stay on one XCD.
@@ -25,7 +26,8 @@
 // move half the accumulator bytes per product of 32x32x16 ones and so let the clock
 // rise, buffer loads (with global_load_lds the compiler waits for every LDS read in
 // flight, lgkmcnt(0), before each use; with buffer loads it counts), and four waves
-// where both operands are K-contiguous.  K-major operands keep eight: their fragments
+// where both operands are K-contiguous, the contraction is long and the tiles are many
+// (fwd_eight_waves).  K-major operands keep eight: their fragments
 // take twice the reads, and one wave per SIMD leaves those exposed (dW1/dW3 of one
 // 2048-token sequence 207 us against 226).  Measured on one card, 64 experts x 2071
 // rows, d 2048, h 1024, against 32x32x16 MFMAs, eight waves and global loads: W1/W3 1053
@@ -216,7 +218,7 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmParams& p, const TileCoo
   constexpr int MB = WM / 16, NB = WN / 16, MH = MB / 2, NH = NB / 2;
   constexpr int KK = KSTEP / 32;
   static_assert(KSTEP == 64 && MB % 2 == 0 && NB % 2 == 0, "two 32-wide sub-steps, whole halves");
-  static_assert(STAGES >= 2 && STAGES <= 5, "ring depth");
+  static_assert(STAGES == 2 || (STAGES == 3 && A_KC && B_KC), "ring depth");
   using OA = DmaOperand<BM, A_KC, NT, KSTEP>;
   using OB = DmaOperand<BN, B_KC, NT, KSTEP>;
   constexpr int STAGE_BYTES = OA::BYTES + OB::BYTES;
@@ -332,7 +334,7 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmParams& p, const TileCoo
   // Issues k-step kt; the calls come with kt = 0, 1, 2, ... in order.
   // Loads [lo, hi) of k-step kt (A's loads first, then B's); each load of a
   // k-step is issued exactly once and the k-steps in order.
-  // K-major rows past the valid K read the zero block; with full_step (a step
+  // K-major rows past the valid K read zero (see BUF_PAST); with full_step (a step
   // known to lie below both kv) the per-load check is skipped.  first: k-step
   // 0 (its successor's source rows are already at hand).
   auto issue_part = [&](int kt, int stage, int lo, int hi, auto full_step, auto first) {
@@ -455,12 +457,11 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmParams& p, const TileCoo
   // for j = 0 and min(STAGES-2, KT-1-j) afterwards (vmcnt counts this wave's
   // outstanding loads, which complete in order).
   auto wait_younger = [&](int younger) {
-    if (younger >= 3) __builtin_amdgcn_s_waitcnt(vmcnt_imm(3 * LOADS));
-    else if (younger == 2) __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * LOADS));
-    else if (younger == 1) __builtin_amdgcn_s_waitcnt(vmcnt_imm(LOADS));
+    if (STAGES > 2 && younger == 2) __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * LOADS));
+    else if (younger >= 1) __builtin_amdgcn_s_waitcnt(vmcnt_imm(LOADS));
     else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
   };
-  static_assert(3 * LOADS <= 63, "vmcnt range");
+  static_assert((STAGES - 1) * LOADS <= 63, "vmcnt range");
   const int KT = (p.K + KSTEP - 1) / KSTEP;
   if (KT > 0) issue(0, 0, std::true_type{});
 #pragma unroll
@@ -577,13 +578,12 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmParams& p, const TileCoo
     using T_ = std::true_type;
     using F_ = std::false_type;
     int kt = 0;
-    // refills of the steps below KT - 1 skip the K-major row check when
-    // every such step lies below both kv (the usual case: only the last step
-    // is ragged); with a split refill, so does the second half of such a
-    // refill in the next step
-    const bool full_ok = p.kv_a >= (KT - 1) * KSTEP && p.kv_b >= (KT - 1) * KSTEP;
-    const int n_full = full_ok ? KT - STAGES - 1 : 0;
     if constexpr (SPLIT_DMA) {
+      // refills of the steps below KT - 1 skip the K-major row check when
+      // every such step lies below both kv (the usual case: only the last step
+      // is ragged), and so does the second part of such a refill in the next step
+      const bool full_ok = p.kv_a >= (KT - 1) * KSTEP && p.kv_b >= (KT - 1) * KSTEP;
+      const int n_full = full_ok ? KT - STAGES - 1 : 0;
       if (KT > STAGES) {
         kstep(0, T_{}, F_{}, F_{});
         if constexpr (!A_KC || !B_KC)
@@ -593,7 +593,6 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmParams& p, const TileCoo
         ++kt;
       }
     } else {
-      for (; kt < n_full; ++kt) kstep(kt, T_{}, F_{}, T_{});
       for (; kt + STAGES < KT; ++kt) kstep(kt, T_{}, F_{}, F_{});
     }
     for (; kt < KT; ++kt) kstep(kt, F_{}, F_{}, F_{});
@@ -925,18 +924,23 @@ hipError_t run_dma_var(GemmParams p, long max_rows, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Row blocks of the forward expert products: 192 when they pad the expert
-// buffers enough less than blocks of 256 (one 2048-token sequence at c(t) =
-// 12 - 8t has 373 rows per expert: 384 computed instead of 512).  A 192-row tile (96 x 128
-// per wave) does three quarters of a 256-row tile's work in 0.875 of its time, so a
-// computed row costs 7/6 as much.  Every choice keeps an expert's row blocks side by
-// side on one XCD, so its weights are fetched once.
+// Row blocks of the forward expert products: 192 when they pad the expert buffers to less
+// than 6/7 of what whole blocks of 256 would (one 2048-token sequence at c(t) = 12 - 8t has
+// 373 rows per expert: 384 instead of 512).  Equal blocks are the faster also where blocks
+// of 256 with a short last one compute no more rows, or fewer, as every round of tiles then
+// takes as long as its fullest: two blocks of 192 against 256 and a short one, 257 rows
+// W2 of 64 experts, d 2048, h 1024 106 and 117 us, of 8 experts 21.5 and 26.3, W1/W3 193
+// and 191, 34.3 and 40.4; 384 rows 115 and 121, 22.0 and 26.8, 198 and 197, 35.0 and 39.5;
+// three, 513 rows 168 and 166, 22.8 and 27.9, 279 and 286, 36.3 and 45.5.  (W1/W3 of many
+// experts is the exception, by up to 4%: 40 experts, d 1472, h 832, 300 rows 98 and 95.)
+// Every choice keeps an expert's row blocks side by side on one XCD, so its weights are
+// fetched once.
 // Buffers of at most 128 or 64 rows (that sequence at t = 1; a short sequence) are one
 // row block that only streams the weights: what counts is loads in flight, so three
 // stages instead of two, and for 64 rows 64 x 128 tiles, two workgroups a CU.  Measured
-// with 64 experts, d 2048, h 1024 (805 MB of weights; 128-row tiles of two stages
-// before): 32 rows W1/W3 132 -> 110 us (4.9 TB/s) and W2 57 -> 50, 128 rows 142 -> 132
-// and 69 -> 62.  64-wide columns, two or four stages and 32-row tiles are all slower.
+// with 64 experts, d 2048, h 1024 (805 MB of weights; 128-row tiles of two stages and
+// eight waves before): 30 rows W1/W3 131 -> 108 us (4.9 TB/s) and W2 57 -> 50, 128 rows 134
+// -> 128 and 65 -> 57.  64-wide columns, two or four stages and 32-row tiles are all slower.
 int fwd_block_rows(int M) {
   if (M <= 64) return 64;
   if (M <= 128) return 128;

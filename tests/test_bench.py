@@ -17,7 +17,8 @@ ROOT = bench.ROOT
 @pytest.mark.parametrize("name,stage", [
     ("void ec::(anonymous namespace)::gemm_dma_kernel<256, 256, 2, 4, 64, 2, true, true, 1, false, "
      "1, 0>(ec::(anonymous namespace)::GemmParams)", "gemm_w13_swiglu"),
-    ("gemm_dma_kernel<192, 256, 2, 4, 64, 2, true, true, 1, false, 1, 0>", "gemm_w13_swiglu"),
+    ("gemm_dma_kernel<192, 256, 2, 2, 64, 2, true, true, 1, false, 1, 0>", "gemm_w13_swiglu"),
+    ("gemm_dma_kernel<128, 128, 2, 2, 64, 3, true, true, 1, false, 1, 0>", "gemm_w13_swiglu"),
     ("gemm_dma_kernel<192, 256, 2, 4, 64, 2, true, true, 0, false, 2, 0>", "gemm_w2"),
     ("gemm_dma_kernel<256, 256, 4, 2, 64, 2, true, false, 2, false, 3, 0>", "gemm_dA_swiglu_bwd"),
     ("gemm_dma_kernel<256, 256, 4, 2, 64, 2, false, false, 0, false, 6, 2>", "gemm_dW13"),
@@ -26,11 +27,12 @@ ROOT = bench.ROOT
     ("void ec::combine_kernel<unsigned short, 64, true>(int)", "bwd_combine"),
     ("combine_kernel<float, 64, false>", "combine"),
     ("router_softmax_bf16_kernel<4, 4>", "router"),
-    ("router_softmax_f32_kernel", "router"),
+    ("router_softmax_f32_kernel<256>", "router"),
     ("topk_col_kernel<8, 4>", "topk"),
-    ("topk_kernel<true>", "topk"),
-    ("router_dz_kernel<8>", "router_dz"),
-    ("splitk_reduce_kernel", "router_dwg_reduce"),
+    ("topk_kernel", "topk"),
+    ("router_dz_kernel<8, unsigned short>", "router_dz"),
+    ("splitk_store_kernel<float>", "router_dwg_reduce"),
+    ("splitk_store_kernel<unsigned short>", None),   # the shared experts' weight gradients
     ("at::native::vectorized_elementwise_kernel<4, at::native::FillFunctor<float>>", None),
 ])
 def test_stage_of_kernel(name, stage):

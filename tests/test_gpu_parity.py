@@ -376,8 +376,8 @@ def test_f32_router_tiles(lens, d, E):
 
 
 def test_long_group_route_only():
-    # a column longer than the LDS-cached top-k path
-    wl = synth.small("long", [20000, 777], 64, 4, 64, seed=18, capacity_factor=1.5)
+    # a column longer than the register forms of the top-k, a short one beside it
+    wl = synth.small("long", [40000, 777], 64, 4, 64, seed=18, capacity_factor=1.5)
     inp = synth.draw(wl)
     caps = caps_for(wl, inp)
     check_route(inp, caps, 1.0)
@@ -387,10 +387,10 @@ def test_long_group_route_only():
                                   [9000, 100], [13000, 5]])
 @pytest.mark.parametrize("ties", [False, True])
 def test_topk_every_path(lens, ties):
-    """Every selection path: one wave per column with 8, 32 or 64 keys per lane
-    (columns up to 512, 2048, 4096 tokens), then one workgroup per column with the
-    keys cached in LDS (up to 12288) or re-read; normal scores and scores with
-    whole runs of bitwise-equal values; capacities from 0 to the whole group."""
+    """The selection's forms of 1, 4, 8 and 16 waves per column (up to 512, 2048, 4096
+    and 16384 tokens; test_topk_long_columns has the longer ones); normal scores and
+    scores with whole runs of bitwise-equal values; capacities from 0 to the whole
+    group."""
     wl = synth.small("paths", lens, 64, 8, 64, seed=23, capacity_factor=1.0)
     inp = synth.draw(wl)
     if ties:
