@@ -146,10 +146,11 @@ __device__ __forceinline__ void dma16(const void* g, void* lds) {
 // The same from a buffer resource: a uniform base, a 32-bit byte offset per lane and a
 // uniform one, so a K-contiguous operand's loads need one register each and no vector
 // arithmetic per step.
-// What a base reaches ends below BUF_BYTES: an ungathered K-contiguous A starts at its
-// tile's first row, so its offsets span one tile however many rows there are (the router's
-// dZ, [N, E rounded up to 64], passes 2^32 bytes); X and dY, read gathered, are below 2^31
-// bytes (N 2 d < 2^31 elements); run_dma checks the others.  A load at BUF_PAST reads zero.
+// What a base reaches ends below BUF_BYTES: the operands that are read gathered, X and dY,
+// are below 2^31 bytes (N 2 d < 2^31 elements), and run_dma checks the others.  Only the
+// router's dZ, [N, E rounded up to 64], passes 2^32 bytes: its base is the tile's first row
+// (OPT_TILE_BASE; for every product that costs W2 of 128 experts x 1024 rows 420 -> 427 us).
+// A load at BUF_PAST reads zero.
 constexpr uint32_t BUF_BYTES = 0xffffff80u, BUF_PAST = 0xfffffff0u;
 #if defined(__HIP_DEVICE_COMPILE__)
 using Rsrc = __amdgpu_buffer_rsrc_t;
@@ -208,7 +209,8 @@ __device__ __forceinline__ int km_swz(int k) { return ((k & 3) << 2) | ((k >> 2)
 // Options of an instantiation (bf16; see GemmParams): OPT_GA / OPT_GB gather
 // the rows of a K-major A / B through p.ka_rows / p.kb_rows.  OPT_TAILS:
 // the last row block and column block take a smaller tile where one holds them.
-enum { OPT_GA = 1, OPT_GB = 2, OPT_TAILS = 4 };
+// OPT_TILE_BASE: an ungathered K-contiguous A of any size, addressed tile by tile.
+enum { OPT_GA = 1, OPT_GB = 2, OPT_TAILS = 4, OPT_TILE_BASE = 8 };
 template <int BM, int BN, int WGM, int WGN, int KSTEP, int STAGES, bool A_KC, bool B_KC, int EPI,
           bool OUT_F32, int OPT>
 __device__ __forceinline__ void gemm_dma_tile(const GemmParams& p, const TileCoord& tc,
@@ -255,7 +257,7 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmParams& p, const TileCoo
   // the operand's stage area: 64 chunks, lane -> chunk.
   // Every load has one byte offset from a uniform base (see BUF_BYTES), the step's offset
   // being uniform.  K-contiguous: the chunk in its row (clamped: rows past the end produce
-  // outputs that are not stored), an ungathered A from row m0 on.
+  // outputs that are not stored).
   // K-major: the chunk at k-step 0, its column clamped into the operand likewise; rows
   // past the valid K ask for an offset past the buffer, which reads as zero.
   // K-major gathered (OPT_GA / OPT_GB): the chunk's column; the source rows of
@@ -264,6 +266,8 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmParams& p, const TileCoo
   // load takes its row's with a lane read.  Rows past the valid K re-read a
   // valid row: the other operand, never gathered, reads zeros there.
   constexpr bool GA = (OPT & OPT_GA) != 0 && !A_KC, GB = (OPT & OPT_GB) != 0 && !B_KC;
+  constexpr bool TILE_BASE = (OPT & OPT_TILE_BASE) != 0;
+  static_assert(!TILE_BASE || A_KC, "a K-contiguous A");
   static_assert(((OPT & OPT_GA) == 0 || GA) && ((OPT & OPT_GB) == 0 || GB), "K-major gathers");
   static_assert(!(GA && GB), "one gathered operand: the other zero-fills the ragged K");
   static_assert((!GA || OA::CPR == 32) && (!GB || OB::CPR == 32),
@@ -304,7 +308,7 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmParams& p, const TileCoo
         const int tok = p.a_rows[(size_t)e * p.a_rows_bs + tc.row0 + r];
         a_off[q] = ((uint32_t)tok * (uint32_t)p.lda + lc * 8) * 2;
       } else {
-        a_off[q] = ((uint32_t)(r - m0) * (uint32_t)p.lda + lc * 8) * 2;
+        a_off[q] = ((uint32_t)(TILE_BASE ? r - m0 : r) * (uint32_t)p.lda + lc * 8) * 2;
       }
     } else {
       const int row = id / OA::CPR, lc = (id % OA::CPR) ^ km_swz(row);
@@ -328,7 +332,7 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmParams& p, const TileCoo
   }
   // a SwiGLU wave's rows all lie in W1 or all in W3
   static_assert(EPI != EPI_SWIGLU || (BN / 2) % (OB::LOADS * 8) == 0, "one weight per wave");
-  const bf16_t* const a_base = Ab + (A_KC ? (size_t)m0 * p.lda : 0);
+  const bf16_t* const a_base = TILE_BASE ? Ab + (size_t)m0 * p.lda : Ab;
   const Rsrc a_rsrc = make_rsrc((A_KC ? p.a_rows != nullptr : GA) ? p.A : (const void*)a_base);
   const Rsrc b_rsrc = make_rsrc(EPI == EPI_SWIGLU && wave * OB::LOADS * 8 >= BN / 2 ? B2b : Bb);
   // Issues k-step kt; the calls come with kt = 0, 1, 2, ... in order.
@@ -873,10 +877,12 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void gemm_dma_kernel(GemmParams 
   gemm_dma_tile<BM, BN, WGM, WGN, KSTEP, STAGES, A_KC, B_KC, EPI, OUT_F32, OPT>(p, tc, smem);
 }
 
-// The operands that a tile addresses from their batch's start are within BUF_BYTES.
+// The operands that a tile addresses from their batch's start are within BUF_BYTES (a
+// batch of variable rows has no more of them than p.M).
 template <bool A_KC, bool B_KC, int OPT>
 bool operands_in_reach(const GemmParams& p) {
-  const long a = (A_KC || (OPT & OPT_GA)) ? 0 : 2L * p.kv_a * p.lda;
+  const bool a_far = (OPT & OPT_GA) || (A_KC && p.a_rows) || (OPT & OPT_TILE_BASE);
+  const long a = a_far ? 0 : 2L * (A_KC ? p.M : p.kv_a) * p.lda;
   const long b = (OPT & OPT_GB) ? 0 : 2L * (B_KC ? p.N : p.kv_b) * p.ldb;
   return a <= (long)BUF_BYTES && b <= (long)BUF_BYTES;
 }
@@ -1473,7 +1479,8 @@ hipError_t launch_router_dx(int dtype, const void* dZ, const void* Wg, void* dX,
   p.C = dX; p.c_bs = 0; p.ldc = d;
   if (N == 0) return hipSuccess;
   if (dtype == DT_F32) return run_f32<true, false, EPI_STORE>(p, st);
-  return run_dma<256, 256, 4, 2, 64, 2, true, false, EPI_STORE, false, G_ROUTER_DX>(p, st);
+  return run_dma<256, 256, 4, 2, 64, 2, true, false, EPI_STORE, false, G_ROUTER_DX, OPT_TILE_BASE>(
+      p, st);
 }
 
 hipError_t launch_router_dwg(int dtype, const void* dZ, const void* X, float* dWg, float* part,
