@@ -6,19 +6,19 @@
 // bf16: one pipelined kernel (gemm_dma_kernel) for every product of the
 // forward and backward.  v_mfma_f32_16x16x32_bf16 with fp32 accumulation; a
 // 256 x 256 output tile per workgroup (the forward products take 192-, 128- or 64-row
-// tiles when those pad short expert buffers less).  K advances 64 at a time through an LDS
-// ring of two stages (three for buffers of one short row block) filled straight from global memory by buffer_load_dwordx4 ... lds
-// (no VGPR staging, one offset register per load).  K-contiguous operands sit in LDS as
-// 128-byte rows with XOR-swizzled 16-byte chunks (conflict-free fragment reads);
-// K-major operands (the weight gradients' token-row contractions, and the weights in
-// the dA and dX products) stay K-major in LDS and are read with the transposing
-// ds_read_b64_tr_b16.  The MFMAs alternate with the next sub-step's fragment reads
-// and, once the barrier has freed a stage, with its refill's DMA (with two stages half of
-// it then, three quarters where both operands are K-contiguous, the rest in the next
-// step), so LDS latency hides behind MFMAs in flight.  The MFMAs
-// take the B fragment first, so each lane ends with four consecutive output columns
-// of a row, staged through LDS with 16-byte writes for coalesced stores.  Tiles are
-// numbered so that consecutive ones share an expert and stay on one XCD.
+// tiles when those pad short expert buffers less).  K advances 64 at a time through an
+// LDS ring of two stages (three for buffers of one short row block) filled straight from
+// global memory by buffer_load_dwordx4 ... lds (no VGPR staging, one offset register per
+// load).  K-contiguous operands sit in LDS as 128-byte rows with XOR-swizzled 16-byte
+// chunks (conflict-free fragment reads); K-major operands (the weight gradients' token-row
+// contractions, and the weights in the dA and dX products) stay K-major in LDS and are read
+// with the transposing ds_read_b64_tr_b16.  The MFMAs alternate with the next sub-step's
+// fragment reads and, once the barrier has freed a stage, with its refill's DMA (with two
+// stages half of it then, three quarters where both operands are K-contiguous, the rest in
+// the next step), so LDS latency hides behind MFMAs in flight.  The MFMAs take the B
+// fragment first, so each lane ends with four consecutive output columns of a row, staged
+// through LDS with 16-byte writes for coalesced stores.  Tiles are numbered so that
+// consecutive ones share an expert and stay on one XCD.
 //
 // What bounds it: at 8 x 2048 tokens the chip's power limit and the LDS port, which a
 // k-step keeps busy about as long as the matrix cores (64 KiB written, 128 KiB read by
@@ -946,7 +946,8 @@ hipError_t run_dma_var(GemmParams p, long max_rows, hipStream_t st) {
 // stages instead of two, and for 64 rows 64 x 128 tiles, two workgroups a CU.  Measured
 // with 64 experts, d 2048, h 1024 (805 MB of weights; 128-row tiles of two stages and
 // eight waves before): 30 rows W1/W3 131 -> 108 us (4.9 TB/s) and W2 57 -> 50, 128 rows 134
-// -> 128 and 65 -> 57.  64-wide columns, two or four stages and 32-row tiles are all slower.
+// -> 128 and 65 -> 57.  Two stages are slower at 128 rows (64 experts 132 and 61); 64-wide
+// columns, four stages and 32-row tiles were, with 32x32x16 MFMAs.
 int fwd_block_rows(int M) {
   if (M <= 64) return 64;
   if (M <= 128) return 128;
@@ -957,8 +958,8 @@ int fwd_block_rows(int M) {
 // Waves of the forward products' 256- and 192-row tiles: four of 128 x 128 read a third
 // less LDS and draw less power, which pays while the chip is full for long; eight of 128 x
 // 64 share a tile's prologue and epilogue out further and hide more latency, which pays
-// where a contraction is short or the tiles fill half the chip once (kept to that for W2,
-// whose eight-wave stores are the slower on some cards: 64 experts x 256 rows, d 1024, h
+// where a contraction is short or the tiles fill half the chip once (only the latter for
+// W2, which is much the slower in eight on some cards: 64 experts x 256 rows, d 1024, h
 // 512, 256 tiles, 22.0 us in four and 26.5 in eight).  Measured, four against eight: W1/W3
 // of 64 experts x 2048 rows, d 2048, h 1024 847 and 872 us; d 1024, h 512 237 and 246 (512
 // rows 63.3 and 60.5); d 640, h 384, 1400 rows 105 and 97; d 512, h 256, 256 rows 19.6 and
