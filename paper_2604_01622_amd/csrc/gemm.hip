@@ -956,19 +956,20 @@ int fwd_block_rows(int M) {
 }
 
 // Waves of the forward products' 256- and 192-row tiles: four of 128 x 128 read a third
-// less LDS and draw less power, which pays while the chip is full for long; eight of 128 x
-// 64 share a tile's prologue and epilogue out further and hide more latency, which pays
-// where a contraction is short or the tiles fill half the chip once (only the latter for
-// W2, which is much the slower in eight on some cards: 64 experts x 256 rows, d 1024, h
-// 512, 256 tiles, 22.0 us in four and 26.5 in eight).  Measured, four against eight: W1/W3
-// of 64 experts x 2048 rows, d 2048, h 1024 847 and 872 us; d 1024, h 512 237 and 246 (512
-// rows 63.3 and 60.5); d 640, h 384, 1400 rows 105 and 97; d 512, h 256, 256 rows 19.6 and
-// 17.4; 32 experts, d 768, h 1536, 512 rows (768 tiles) 77.6 and 81.5; 8 experts, d 2048,
-// h 1024, 512 rows (128 tiles) 44.0 and 42.3, W2 there 27.4 and 26.2 (d 1024, h 512 17.4
-// and 16.2).
-bool fwd_eight_waves(int epi, long tiles, int k) {
+// less LDS, draw less power and store wider rows (128 bytes of each W1/W3 output where
+// eight store 64), which pays while the chip is full for long and where H1 and H3 are
+// saved; eight of 128 x 64 share a tile's prologue and epilogue out further and hide more
+// latency, which pays where the tiles fill half the chip once, and in W1/W3 without saved
+// outputs where a contraction is short.  Measured, four against eight: W1/W3 of 64 experts
+// x 2048 rows, d 2048, h 1024 847 and 872 us; d 1024, h 512 237 and 246 (512 rows 63.3 and
+// 60.5, saving 69.8 and 75.6); d 640, h 384, 1400 rows 105 and 97; d 512, h 256, 256 rows
+// 19.6 and 17.4, 1024 rows 39.5 and 36.0, saving 46.7 and 59.3; 32 experts, d 768, h 1536,
+// 512 rows (768 tiles) 77.6 and 81.5; 8 experts, d 2048, h 1024, 512 rows (128 tiles) 44.0
+// and 42.3, saving 46.1 and 44.2; W2 there 27.4 and 26.2 (d 1024, h 512 17.4 and 16.2),
+// but of 64 experts x 256 rows, d 1024, h 512 (256 tiles) 22.0 and, on some cards, 26.5.
+bool fwd_eight_waves(int epi, long tiles, int k, bool saves) {
   if (tiles <= 128) return true;
-  return epi == EPI_SWIGLU && (k <= 704 || (k <= 1024 && tiles <= 512));
+  return epi == EPI_SWIGLU && !saves && (k <= 704 || (k <= 1024 && tiles <= 512));
 }
 
 // A forward product in BM x 256 tiles of four or eight waves.
@@ -986,8 +987,8 @@ hipError_t run_fwd(const GemmParams& p, hipStream_t st, long max_rows = 0) {
     else
       return run_dma<BM, 256, 2, WGN, 64, 2, true, true, EPI, false, TAG, OPT>(p, st);
   };
-  return fwd_eight_waves(EPI, tiles, p.K) ? run(std::integral_constant<int, 4>{})
-                                          : run(std::integral_constant<int, 2>{});
+  return fwd_eight_waves(EPI, tiles, p.K, p.H1 != nullptr) ? run(std::integral_constant<int, 4>{})
+                                                             : run(std::integral_constant<int, 2>{});
 }
 
 // Buffers of one 128-row block (three stages): 128 x 128 tiles of four waves while there
